@@ -133,10 +133,13 @@ template <typename T> Phys<T> make_phys(const mhd_ctx *ctx, double ch)
     p.gamma = (T)g;
     p.gm1 = (T)(g - 1.0);
     p.inv_gm1 = (T)(1.0 / (g - 1.0));
+    p.inv_gm1m1 = (T)(1.0 / (g - 1.0) - 1.0);
     p.glm = ctx->cfg.glm ? 1 : 0;
     p.ch = (T)(p.glm ? ch : 0.0);
     p.ch2 = (T)(p.glm ? ch * ch : 0.0);
     p.half_ich = (T)(p.glm ? 0.5 / ch : 0.0);
+    p.half_ch = (T)(p.glm ? 0.5 * ch : 0.0);
+    p.half_on = (T)(p.glm ? 0.5 : 0.0);
     return p;
 }
 

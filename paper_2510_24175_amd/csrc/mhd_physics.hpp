@@ -104,14 +104,77 @@ template <> struct Num<double> {
     static constexpr double big = 1.0e300;
 };
 
+// Selections by sign masks.  A VOP2 v_cndmask_b32, which reads its condition
+// from VCC, issues every ~23 cycles in a run of them on gfx950, and a compare
+// costs another slow slot; v_bfi_b32 with a mask made by an arithmetic shift of
+// a sign bit issues every 4.4 cycles and needs no compare (FP32 add, multiply,
+// FMA and 32-bit logic: 2.4; minimum, maximum, median, compare: 4.4; FP64: 4.6;
+// FP32 rcp, sqrt, rsq: 8.2; FP64: 16.3; four waves per SIMD, 2.4 GHz).  The
+// empty asm hides the mask's origin, or the compiler turns the bit operations
+// back into compares and v_cndmask.
+template <typename T> struct Bits;
+
+template <> struct Bits<float> {
+    static __device__ __forceinline__ unsigned word(float x) { return __builtin_bit_cast(unsigned, x); }
+    // all ones where x has its sign bit set, else zero
+    static __device__ __forceinline__ unsigned negative(float x) { return opaque((int)word(x) >> 31); }
+    // all ones where the sign bits of x and y differ
+    static __device__ __forceinline__ unsigned differ(float x, float y) { return opaque((int)(word(x) ^ word(y)) >> 31); }
+    // m ? a : b, bit by bit
+    static __device__ __forceinline__ float select(unsigned m, float a, float b)
+    {
+        return __builtin_bit_cast(float, (word(a) & m) | (word(b) & ~m));
+    }
+    // m ? a : 0
+    static __device__ __forceinline__ float keep(unsigned m, float a) { return __builtin_bit_cast(float, word(a) & m); }
+    // a with its sign flipped where s is negative
+    static __device__ __forceinline__ float flip(float a, float s)
+    {
+        return __builtin_bit_cast(float, word(a) ^ (word(s) & 0x80000000u));
+    }
+    static __device__ __forceinline__ unsigned opaque(int m)
+    {
+        asm("" : "+v"(m));
+        return (unsigned)m;
+    }
+};
+
+template <> struct Bits<double> {
+    struct Words { unsigned lo, hi; };
+    static __device__ __forceinline__ Words words(double x) { return __builtin_bit_cast(Words, x); }
+    static __device__ __forceinline__ unsigned negative(double x) { return Bits<float>::opaque((int)words(x).hi >> 31); }
+    static __device__ __forceinline__ unsigned differ(double x, double y)
+    {
+        return Bits<float>::opaque((int)(words(x).hi ^ words(y).hi) >> 31);
+    }
+    static __device__ __forceinline__ double select(unsigned m, double a, double b)
+    {
+        const Words x = words(a), y = words(b);
+        return __builtin_bit_cast(double, Words{(x.lo & m) | (y.lo & ~m), (x.hi & m) | (y.hi & ~m)});
+    }
+    static __device__ __forceinline__ double keep(unsigned m, double a)
+    {
+        const Words x = words(a);
+        return __builtin_bit_cast(double, Words{x.lo & m, x.hi & m});
+    }
+    static __device__ __forceinline__ double flip(double a, double s)
+    {
+        const Words x = words(a);
+        return __builtin_bit_cast(double, Words{x.lo, x.hi ^ (words(s).hi & 0x80000000u)});
+    }
+};
+
 // Per-launch constants of the scheme.
 template <typename T> struct Phys {
     T gamma;     // adiabatic index
     T gm1;       // gamma - 1
     T inv_gm1;   // 1 / (gamma - 1)
+    T inv_gm1m1; // 1 / (gamma - 1) - 1
     T ch;        // GLM wave speed c_h
     T ch2;       // c_h^2
     T half_ich;  // 1 / (2 c_h), 0 when GLM is off
+    T half_ch;   // c_h / 2, 0 when GLM is off
+    T half_on;   // 1/2, 0 when GLM is off
     int glm;     // GLM cleaning on
 };
 
@@ -340,113 +403,134 @@ __device__ __forceinline__ void hll_flux(const RState<T> &L, const RState<T> &R,
     }
 }
 
-// One side of the HLLD single-star state (Miyoshi & Kusano 2005): density,
-// tangential velocity and field.  Its energy is formed only for the side the
-// flux is taken from (hlld_star_energy).
+// One side of an interface in the rotated frame: primitives, transverse field
+// squared, total pressure.
+template <typename T> struct Side {
+    T rho, u, v1, v2, p, b1, b2, bt2, pt;
+};
+
+template <typename T> __device__ __forceinline__ void side_prepare(Side<T> &s, T bn)
+{
+    s.bt2 = s.b1 * s.b1 + s.b2 * s.b2;
+    s.pt = s.p + T(0.5) * (bn * bn + s.bt2);
+}
+
+// twice the square of the fast speed: c_f^2 = (g p + |B|^2 + sqrt((g p - |B|^2)^2
+// + 4 g p |B_t|^2)) / (2 rho)
+template <typename T>
+__device__ __forceinline__ T fast_sq2(const Side<T> &s, T bn2, const Phys<T> &ph)
+{
+    const T gp = ph.gamma * s.p, bsq = bn2 + s.bt2;
+    const T d = gp - bsq;
+    const T disc = Num<T>::max(T(4) * gp * s.bt2 + d * d, T(0));
+    return ((gp + bsq) + Num<T>::sqrt(disc)) * Num<T>::rcp(s.rho);
+}
+
+// total energy density (|B|^2/2 = p_T - p) and v.B
+template <typename T>
+__device__ __forceinline__ T side_energy(const Side<T> &s, const Phys<T> &ph)
+{
+    return T(0.5) * s.rho * (s.u * s.u + s.v1 * s.v1 + s.v2 * s.v2) + (s.p * ph.inv_gm1m1 + s.pt);
+}
+template <typename T> __device__ __forceinline__ T side_vb(const Side<T> &s, T bn)
+{
+    return s.u * bn + s.v1 * s.b1 + s.v2 * s.b2;
+}
+
+// One side of the HLLD single-star state (Miyoshi & Kusano 2005).  With
+// m = rho (S - u) and mm = m (S - S_M) > 0, r = 1/sqrt(mm) gives the star
+// density's root q = m r (negative on the left; rho* = q^2), 1/q = (S - S_M) r
+// and 1/(S - S_M) = q r without further reciprocals.  With w = S_M - u and
+// D = mm - B_n^2: v* = v - B_t B_n w / D and B* = B_t (1 + m w / D).
 template <typename T> struct Star {
-    T rho, v1, v2, b1, b2;
-    T su, isd; // S - u and 1/(S - S_M)
-    T sq, isq; // sqrt(rho*) and 1/sqrt(rho*)
+    T v1, v2, b1, b2;
+    T sd;    // S - S_M
+    T q, r;  // m r, 1/sqrt(m (S - S_M))
+    T a;     // (S - u) E - p_T u + B_n v.B, the side's own share of E* (S - S_M)
 };
 
 template <typename T>
-__device__ __forceinline__ void hlld_star(const RState<T> &s, T S, T sM, Star<T> &o)
+__device__ __forceinline__ void hlld_star(const Side<T> &s, T S, T su, T m, T w, T sM, T bn, T bn2,
+                                          const Phys<T> &ph, Star<T> &o)
 {
-    o.su = S - s.u;
-    o.isd = Num<T>::rcp(S - sM);
-    const T m = s.rho * o.su;
-    o.rho = m * o.isd;
-    const T mm = m * (S - sM);
-    const T bn2 = s.bn * s.bn;
+    o.sd = S - sM;
+    const T mm = m * o.sd;
     const T D = mm - bn2;
-    const bool degenerate = Num<T>::abs(D) <= T(16) * Num<T>::eps * (Num<T>::abs(mm) + bn2);
-    const T iD = Num<T>::rcp(D);
-    // a degenerate side keeps its tangential state: cv = 0, cb = 1
-    const T cv = degenerate ? T(0) : s.bn * (sM - s.u) * iD;
-    const T cb = degenerate ? T(1) : (m * o.su - bn2) * iD;
+    // degenerate side, |D| <= 16 eps (mm + B_n^2): 1/D <- 0 keeps its tangential state
+    const T tol = T(16) * Num<T>::eps * mm + T(16) * Num<T>::eps * bn2;
+    const T x = w * Bits<T>::keep(Bits<T>::negative(tol - Num<T>::abs(D)), Num<T>::rcp(D));
+    const T cv = bn * x, cb = m * x;
     o.v1 = s.v1 - s.b1 * cv;
     o.v2 = s.v2 - s.b2 * cv;
-    o.b1 = s.b1 * cb;
-    o.b2 = s.b2 * cb;
-    o.isq = Num<T>::rsqrt(o.rho);
-    o.sq = o.rho * o.isq;
+    o.b1 = s.b1 + s.b1 * cb;
+    o.b2 = s.b2 + s.b2 * cb;
+    o.r = Num<T>::rsqrt(mm);
+    o.q = m * o.r;
+    o.a = su * side_energy(s, ph) - s.pt * s.u + bn * side_vb(s, bn);
 }
 
-// v*.B* and E* of one side: E* = ((S-u)E - p_T u + p_T* S_M + B_n (v.B - v*.B*)) / (S - S_M)
+// HLLD flux (Miyoshi & Kusano 2005; slots rho, m_n, m_1, m_2, E, unused, B_1,
+// B_2), outer speeds
+// min(u_L, u_R) - max(c_fL, c_fR) and max(u_L, u_R) + max(c_fL, c_fR).  The star
+// states satisfy the jump conditions across the outer and the rotational
+// waves, so the flux in a star region is the physical flux of the region's
+// state, with normal velocity S_M and total pressure p_T*: one state is
+// picked and its flux formed, instead of adding the jumps wave by wave.  At
+// a supersonic interface (the fan on one side of the face) S_M <- u of the
+// upwind side makes that side's star state the side's own state.
 template <typename T>
-__device__ __forceinline__ void hlld_star_energy(const RState<T> &s, const Star<T> &o, T sM, T pts,
-                                                 T &vbs, T &Es)
+__device__ __forceinline__ void hlld_flux(const Side<T> &L, const Side<T> &R, T bn, const Phys<T> &ph, T *F)
 {
-    vbs = sM * s.bn + o.v1 * o.b1 + o.v2 * o.b2;
-    Es = (o.su * s.E - s.pt * s.u + pts * sM + s.bn * (s.vb - vbs)) * o.isd;
-}
-
-// HLLD flux (Miyoshi & Kusano 2005), outer speeds min(u_L, u_R) - max(c_fL,
-// c_fR) and max(u_L, u_R) + max(c_fL, c_fR).  L and R need
-// irho, bsq and pt (rstate_prepare); E and v.B are formed for the side the
-// flux is taken from.
-template <typename T>
-__device__ __forceinline__ void hlld_flux(const RState<T> &L, const RState<T> &R,
-                                          const Phys<T> &ph, T *F)
-{
+    const T bn2 = bn * bn;
     // outer speeds: the slower (faster) normal velocity minus (plus) the
     // larger fast speed (at least as wide as Davis's bounds; keeps the
     // rotational waves inside the fan where Davis's bounds let D cross zero)
-    const T cL = rstate_fast(L, ph), cR = rstate_fast(R, ph);
-    const T cm = Num<T>::max(cL, cR);
+    const T cm = Num<T>::sqrt(T(0.5) * Num<T>::max(fast_sq2(L, bn2, ph), fast_sq2(R, bn2, ph)));
     const T sL = Num<T>::min(L.u, R.u) - cm;
     const T sR = Num<T>::max(L.u, R.u) + cm;
-    const T mL = (sL - L.u) * L.rho, mR = (sR - R.u) * R.rho;
-    const T idm = Num<T>::rcp(mR - mL);
-    const T sM = (mR * R.u - mL * L.u - R.pt + L.pt) * idm;
-    const T pts = (mR * L.pt - mL * R.pt + mL * mR * (R.u - L.u)) * idm;
-    const T bn = L.bn;
+    const T suL = sL - L.u, suR = sR - R.u;
+    const T mL = suL * L.rho, mR = suR * R.rho;
+    // contact speed; the upwind normal velocity when the fan lies on one side
+    const T sC = (mR * R.u - mL * L.u + (L.pt - R.pt)) * Num<T>::rcp(mR - mL);
+    const T sM = Bits<T>::select(Bits<T>::negative(sR), R.u, Bits<T>::select(Bits<T>::negative(sL), sC, L.u));
+    const T wL = sM - L.u, wR = sM - R.u;
 
     Star<T> sl, sr;
-    hlld_star(L, sL, sM, sl);
-    hlld_star(R, sR, sM, sr);
+    hlld_star(L, sL, suL, mL, wL, sM, bn, bn2, ph, sl);
+    hlld_star(R, sR, suR, mR, wR, sM, bn, bn2, ph, sr);
 
-    const T sgn = bn >= T(0) ? T(1) : T(-1);
-    const T abn = Num<T>::abs(bn);
-    const T ssL = sM - abn * sl.isq;
-    const T ssR = sM + abn * sr.isq;
-    const T iden = Num<T>::rcp(sl.sq + sr.sq);
-    const T v1 = (sl.sq * sl.v1 + sr.sq * sr.v1 + (sr.b1 - sl.b1) * sgn) * iden;
-    const T v2 = (sl.sq * sl.v2 + sr.sq * sr.v2 + (sr.b2 - sl.b2) * sgn) * iden;
-    const T sqq = sl.sq * sr.sq;
-    const T b1 = (sl.sq * sr.b1 + sr.sq * sl.b1 + sqq * (sr.v1 - sl.v1) * sgn) * iden;
-    const T b2 = (sl.sq * sr.b2 + sr.sq * sl.b2 + sqq * (sr.v2 - sl.v2) * sgn) * iden;
-    const T vbss = sM * bn + v1 * b1 + v2 * b2;
+    // double-star tangential state
+    const T iden = Num<T>::rcp(sr.q - sl.q);
+    const T wl = -sl.q * iden, wr = sr.q * iden;
+    const T si = Bits<T>::flip(iden, bn), sx = -sl.q * sr.q * si;
+    const T dv1 = sr.v1 - sl.v1, dv2 = sr.v2 - sl.v2, db1 = sr.b1 - sl.b1, db2 = sr.b2 - sl.b2;
+    const T v1ss = sl.v1 + wr * dv1 + si * db1, v2ss = sl.v2 + wr * dv2 + si * db2;
+    const T b1ss = sl.b1 + wl * db1 + sx * dv1, b2ss = sl.b2 + wl * db2 + sx * dv2;
 
-    // side of the contact and the region within it
-    const bool left = sM >= T(0);
-    RState<T> S = left ? L : R;
-    rstate_energy(S, ph);
-    const Star<T> st = left ? sl : sr;
-    const T s_out = left ? sL : sR;
-    const T s_in = left ? ssL : ssR;
-    // outer region: sL >= 0 (left) or sR <= 0 (right)
-    const bool outer = left ? (sL >= T(0)) : (sR <= T(0));
-    // double-star region: s*L < 0 (left of contact) or s*R >= 0 (right)
-    const bool dbl = left ? (ssL < T(0)) : (ssR >= T(0));
-    const T a1 = outer ? T(0) : s_out;
-    const T a2 = (outer || !dbl) ? T(0) : s_in;
-    T vbs, Es;
-    hlld_star_energy(S, st, sM, pts, vbs, Es);
-    const T Ess = Es + (left ? -st.sq : st.sq) * (vbs - vbss) * sgn;
-
-    T f[8], u[8];
-    rstate_flux(S, f, u);
-    const T us[8] = {st.rho, st.rho * sM, st.rho * st.v1, st.rho * st.v2, Es, bn, st.b1, st.b2};
-    const T uss[8] = {st.rho, st.rho * sM, st.rho * v1, st.rho * v2, Ess, bn, b1, b2};
-    // rho, the normal momentum and B_n agree in the single- and double-star
-    // states; slot 5 (B_n) is unused
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        if (k == 5) F[k] = T(0);
-        else if (k <= 1) F[k] = f[k] + a1 * (us[k] - u[k]);
-        else F[k] = f[k] + a1 * (us[k] - u[k]) + a2 * (uss[k] - us[k]);
-    }
+    // side of the contact (right where S_M < 0), then the region within it:
+    // the rotational wave S_M + |B_n|/q of that side lies across the face
+    // when its sign is not S_M's
+    const unsigned right = Bits<T>::negative(sM);
+    auto pick = [&](T l, T r) -> T { return Bits<T>::select(right, r, l); };
+    const T q = pick(sl.q, sr.q), r = pick(sl.r, sr.r), sd = pick(sl.sd, sr.sd), a = pick(sl.a, sr.a);
+    const T pts = pick(L.pt + mL * wL, R.pt + mR * wR);
+    const T v1s = pick(sl.v1, sr.v1), v2s = pick(sl.v2, sr.v2), b1s = pick(sl.b1, sr.b1), b2s = pick(sl.b2, sr.b2);
+    const unsigned dbl = Bits<T>::differ(sM + Num<T>::abs(bn) * (sd * r), sM);
+    const T v1 = Bits<T>::select(dbl, v1ss, v1s), v2 = Bits<T>::select(dbl, v2ss, v2s);
+    const T b1 = Bits<T>::select(dbl, b1ss, b1s), b2 = Bits<T>::select(dbl, b2ss, b2s);
+    const T bs = sM * bn;
+    const T vbs = bs + v1s * b1s + v2s * b2s, vb = bs + v1 * b1 + v2 * b2;
+    // E* = (a + p_T* S_M - B_n v*.B*) / (S - S_M); E** = E* + q sgn(B_n) (v*.B* - v**.B**)
+    const T E = (a + pts * sM - bn * vbs) * (q * r) + Bits<T>::flip(q, bn) * (vbs - vb);
+    const T mu = q * q * sM;
+    F[0] = mu;
+    F[1] = mu * sM + (pts - bn2);
+    F[2] = mu * v1 - bn * b1;
+    F[3] = mu * v2 - bn * b2;
+    F[4] = (E + pts) * sM - bn * vb;
+    F[5] = T(0);
+    F[6] = sM * b1 - bn * v1;
+    F[7] = sM * b2 - bn * v2;
 }
 
 // Select a[d] for d in {0,1,2} without indexing a register array (the
@@ -472,38 +556,39 @@ __device__ __forceinline__ void face_flux(const T *VL, const T *VR, int d, const
     if (CT) {
         bns = bnf;
         psis = T(0);
-    } else if (ph.glm) {
-        bns = T(0.5) * (bnL + bnR) - (VR[PSI] - VL[PSI]) * ph.half_ich;
-        psis = T(0.5) * (VL[PSI] + VR[PSI]) - T(0.5) * ph.ch * (bnR - bnL);
     } else {
-        bns = T(0.5) * (bnL + bnR);
-        psis = T(0);
+        // GLM off: half_ich, half_on and half_ch are zero
+        bns = T(0.5) * (bnL + bnR) - (VR[PSI] - VL[PSI]) * ph.half_ich;
+        psis = ph.half_on * (VL[PSI] + VR[PSI]) - ph.half_ch * (bnR - bnL);
     }
-    RState<T> L, R;
-    L.rho = VL[RHO];
-    L.u = pick3(d, VL[VX], VL[VY], VL[VZ]);
-    L.v1 = pick3(d, VL[VY], VL[VZ], VL[VX]);
-    L.v2 = pick3(d, VL[VZ], VL[VX], VL[VY]);
-    L.p = VL[PRS];
-    L.bn = bns;
-    L.b1 = pick3(d, VL[BY], VL[BZ], VL[BX]);
-    L.b2 = pick3(d, VL[BZ], VL[BX], VL[BY]);
-    R.rho = VR[RHO];
-    R.u = pick3(d, VR[VX], VR[VY], VR[VZ]);
-    R.v1 = pick3(d, VR[VY], VR[VZ], VR[VX]);
-    R.v2 = pick3(d, VR[VZ], VR[VX], VR[VY]);
-    R.p = VR[PRS];
-    R.bn = bns;
-    R.b1 = pick3(d, VR[BY], VR[BZ], VR[BX]);
-    R.b2 = pick3(d, VR[BZ], VR[BX], VR[BY]);
-    rstate_prepare(L);
-    rstate_prepare(R);
+    // a face state in the frame (RState or Side)
+    auto rotate = [&](const T *V, auto &s) {
+        s.rho = V[RHO];
+        s.u = pick3(d, V[VX], V[VY], V[VZ]);
+        s.v1 = pick3(d, V[VY], V[VZ], V[VX]);
+        s.v2 = pick3(d, V[VZ], V[VX], V[VY]);
+        s.p = V[PRS];
+        s.b1 = pick3(d, V[BY], V[BZ], V[BX]);
+        s.b2 = pick3(d, V[BZ], V[BX], V[BY]);
+    };
     T f[8];
-    if (SOLVER == SOLVER_HLLD)
-        hlld_flux(L, R, ph, f);
-    else
+    if constexpr (SOLVER == SOLVER_HLLD) {
+        Side<T> L, R;
+        rotate(VL, L);
+        rotate(VR, R);
+        side_prepare(L, bns);
+        side_prepare(R, bns);
+        hlld_flux(L, R, bns, ph, f);
+    } else {
+        RState<T> L, R;
+        rotate(VL, L);
+        rotate(VR, R);
+        L.bn = R.bn = bns;
+        rstate_prepare(L);
+        rstate_prepare(R);
         hll_flux(L, R, ph, f);
-    const T fbn = (!CT && ph.glm) ? psis : T(0);
+    }
+    const T fbn = psis;
     F[RHO] = f[0];
     F[ENG] = f[4];
     // unrotate: component x is (n, t2, t1) for d = (0, 1, 2), etc.
@@ -513,7 +598,7 @@ __device__ __forceinline__ void face_flux(const T *VL, const T *VR, int d, const
     F[BX] = pick3(d, fbn, f[7], f[6]);
     F[BY] = pick3(d, f[6], fbn, f[7]);
     F[BZ] = pick3(d, f[7], f[6], fbn);
-    F[PSI] = (!CT && ph.glm) ? ph.ch2 * bns : T(0);
+    F[PSI] = CT ? T(0) : ph.ch2 * bns;
 }
 
 // Boundary index map of a ghost or interior coordinate m on an axis of n >= 2

@@ -333,8 +333,8 @@ stage_kernel(const StageArgs<T> a)
         for (int q = 0; q < NQ; ++q) s[q] = limited_slope<LIM>(v0[q] - vm[q], vp[q] - v0[q]);
     };
 
-    // Flux through one face of the plane from its two states, stored (dst
-    // may be null for padding items).  Constrained transport: fc is the cell
+    // Flux through one face of the plane from its two states, stored in LDS.
+    // Constrained transport: fc is the cell
     // whose lower face this is (its face value is the normal field) and, for
     // the tile's own faces (mine), the two transverse field fluxes go to flx.
     auto flux_item = [&](auto dir, const T *VL, const T *VR, T *dst, int fstride, long long fc,
@@ -350,10 +350,8 @@ stage_kernel(const StageArgs<T> a)
         } else {
             face_flux<T, SOLVER>(VL, VR, D, a.ph, F);
         }
-        if (dst) {
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) dst[q * fstride] = F[q];
-        }
+        for (int q = 0; q < NQ; ++q) dst[q * fstride] = F[q];
     };
     // owner cell (in plane zk) of the lower face of tile cell (x, y), and
     // whether that cell is in the grid
@@ -524,6 +522,11 @@ stage_kernel(const StageArgs<T> a)
                 face_flux<T, SOLVER, true>(VL, VR, 2, a.ph, Fzp, a.uin[11 * a.ncell + zoff(k + 1) + own]);
             else
                 face_flux<T, SOLVER>(VL, VR, 2, a.ph, Fzp);
+            // The flux is used after the x/y faces: without a use here the
+            // compiler moves half of the z face past them and keeps its
+            // intermediates (about 40 registers) live across them.
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) asm volatile("" : "+v"(Fzp[q]));
             // slide the window by one plane
 #pragma unroll
             for (int m = 0; m + 1 < ZW; ++m) {
@@ -587,19 +590,16 @@ stage_kernel(const StageArgs<T> a)
             for (int ch = wave; ch < NCHUNK; ch += NW) {
                 T VL[NQ], VR[NQ];
                 if (ch < NCHX) {
-                    const int it = ch * TX + tx;
-                    const bool valid = it < NFX;
-                    const int r = valid ? it / (TX + 1) : 0;
-                    const int f = valid ? it - r * (TX + 1) : 0;
+                    const int it = min(ch * TX + tx, NFX - 1);  // lanes past the last item repeat it
+                    const int r = it / (TX + 1), f = it - r * (TX + 1);
                     constexpr int QS = TY * NXE;
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) {
                         VL[q] = EX[q * QS + r * NXE + f];
                         VR[q] = EX[NQ * QS + q * QS + r * NXE + f + 1];
                     }
-                    flux_item(std::integral_constant<int, 0>{}, VL, VR,
-                              valid ? &FXs[r * (TX + 1) + f] : nullptr, TY * (TX + 1), face_cell(zk, f, r),
-                              valid && f < TX && in_grid(f, r));
+                    flux_item(std::integral_constant<int, 0>{}, VL, VR, &FXs[it], TY * (TX + 1),
+                              face_cell(zk, f, r), f < TX && in_grid(f, r));
                 } else {
                     const int it = (ch - NCHX) * TX + tx;
                     const int r = it / TX, c = it - r * TX;
@@ -620,14 +620,12 @@ stage_kernel(const StageArgs<T> a)
             // compile-time frame.
             for (int ch = wave; ch < NCHUNK; ch += NW) {
                 if (ch < NCHX) {
-                    const int it = ch * TX + tx;
-                    const bool valid = it < NFX;
-                    const int r = valid ? it / (TX + 1) : 0;
-                    const int f = valid ? it - r * (TX + 1) : 0;
+                    // lanes past the last item repeat it (same values, same slot)
+                    const int it = min(ch * TX + tx, NFX - 1);
+                    const int r = it / (TX + 1), f = it - r * (TX + 1);
                     // cells f-2 .. f+1 of row r
-                    face_item(std::integral_constant<int, 0>{}, &P[(r + HY) * PX + f], 1,
-                              valid ? &FXs[r * (TX + 1) + f] : nullptr, TY * (TX + 1), face_cell(zk, f, r),
-                              valid && f < TX && in_grid(f, r));
+                    face_item(std::integral_constant<int, 0>{}, &P[(r + HY) * PX + f], 1, &FXs[it],
+                              TY * (TX + 1), face_cell(zk, f, r), f < TX && in_grid(f, r));
                 } else {
                     const int it = (ch - NCHX) * TX + tx;
                     const int r = it / TX, c = it - r * TX;
