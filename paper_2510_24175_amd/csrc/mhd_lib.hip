@@ -19,6 +19,11 @@
 
 using namespace mhd;
 
+// grid of a marching kernel: column tiles and z chunks of kz planes
+struct Launch {
+    int tiles_x, tiles_y, chunks, kz, nblocks;
+};
+
 struct mhd_ctx {
     mhd_config cfg;
     hipStream_t stream = nullptr;
@@ -34,6 +39,7 @@ struct mhd_ctx {
     void *ct_emf = nullptr;      // constrained transport: [3] edge EMFs
     double *part = nullptr;      // NPART x part_cap block partials
     int part_cap = 0;
+    Launch plan = {};            // grid of the forward stages
     double *result = nullptr;    // device NPART doubles: reductions of the last mhd_step output
     double *cfl_result = nullptr; // device NPART doubles: the last mhd_cfl_dt reduction
     int *flag = nullptr;         // device non-physical flag
@@ -76,34 +82,70 @@ mhd_status fail_hip(mhd_ctx *ctx, const char *what, hipError_t e)
     } while (0)
 
 // Stage tile rows per workgroup (one wave per row; two with FP64 WENO-Z, see
-// stage_row_waves).  FP32 PLM: 4 rows, three
-// workgroups (12 waves) per compute unit at the 168-VGPR budget; measured
-// faster than 6 rows (two workgroups of 6 waves) by a third and than 8 rows
-// (one workgroup of 8 waves) by 13%; an 8-row first stage at two workgroups
-// of 8 waves (125 registers, a tenth fewer face items and half the halo
-// conversions per cell) measured 2% slower, and a 6-row last stage at two
-// workgroups of 6 waves (the same 12 waves per compute unit; 6 waves do not
-// spread evenly over its 4 SIMDs) 60% slower.  FP32 WENO-Z: 8 rows, one workgroup of
-// 8 waves and 155 KB of LDS per compute unit; the three-cell y halo costs
-// half as much per cell as with 4 rows (measured 9% faster).  FP64 (register
-// bound, WENO-Z at 140 KB of LDS): 4 rows.  1D: 1 row.
+// stage_row_waves).  3D PLM: 8 rows (26 face rounds per 512 cells against 28
+// with two 4-row tiles, half the y halo; 512^3 FP32 stages 4.04 + 5.02 -> 3.83 +
+// 4.55 ms, 256^3 FP64 1.26 + 1.44 -> 1.22 + 1.45 ms).  FP32 WENO-Z: 8 rows, one
+// workgroup of 8 waves and 155 KB of LDS per compute unit; the three-cell y
+// halo costs half as much per cell as with 4 rows (measured 9% faster).  FP64
+// WENO-Z (140 KB of LDS) and 2D PLM (a single plane: more, smaller
+// workgroups): 4 rows.  1D: 1 row.
+constexpr int tile_rows_of(bool f32, bool weno, int ndim)
+{
+    return ndim == 1 ? 1 : ((weno ? f32 : ndim == 3) ? 8 : 4);
+}
 template <typename T, int LIM, int NDIM> constexpr int tile_rows()
 {
-    return NDIM == 1 ? 1 : (sizeof(T) == 4 && LIM == LIM_WENOZ ? 8 : 4);
+    return tile_rows_of(sizeof(T) == 4, LIM == LIM_WENOZ, NDIM);
 }
 
-struct Launch {
-    int tiles_x, tiles_y, chunks, kz, nblocks;
-};
+constexpr int COMPUTE_UNITS = 256;
+// block partials any context and the static scratch of mhd_step_noalloc hold
+constexpr int MIN_PART_BLOCKS = 4096;
 
-// min_blocks: the grid size below which z chunks are shortened (each chunk
-// pays a warm-up of a few planes); the forward stages run two or three
-// workgroups per compute unit and want 2048, the adjoint runs one and
-// wants 256: its warm-up is three full planes of z work, and one round of
-// longer chunks measured 4% faster at 128^3 than two rounds of half-length
-// ones.
-Launch plan_stage(const mhd_ctx *ctx, int ty, long long min_blocks = 2048)
+// z chunks of a marching kernel over tiles_x x tiles_y column tiles: the
+// number of chunks that minimises rounds x (planes per chunk + warm-up).  A
+// compute unit holds per_cu workgroups at a time; a round fills all units, and
+// a last round that leaves one workgroup (of two) per unit takes 0.6 of a
+// full one (measured, FP32 PLM).  warm is what starting a chunk costs, in
+// planes.  Chunks have at most 64 planes: longer ones measured no faster and
+// leave the last round's imbalance to chance.  Measured against every
+// power-of-two length (3D PLM, 32^3 to 320^3, both precisions) the choice is
+// within 6% of the best; lengths halved until the grid had 2048 workgroups
+// were up to 30% slower below 200^3.
+Launch plan_march(long long nx, long long ny, long long nz, int ty, int per_cu, double warm)
 {
+    Launch L;
+    L.tiles_x = (int)((nx + TX - 1) / TX);
+    L.tiles_y = (int)((ny + ty - 1) / ty);
+    const long long tiles = (long long)L.tiles_x * L.tiles_y;
+    const int longest = (int)std::min(nz, 64LL);
+    const long long most = std::max((long long)MIN_PART_BLOCKS, tiles * ((nz + longest - 1) / longest));
+    double best = 0.0;
+    L.kz = 0;
+    for (int kz = longest; kz >= 1; --kz) {
+        const long long blocks = tiles * ((nz + kz - 1) / kz);
+        if (blocks > most) break;
+        const long long full = blocks / (COMPUTE_UNITS * per_cu), rest = blocks % (COMPUTE_UNITS * per_cu);
+        const double rounds = (double)full + (rest == 0 ? 0.0 : (rest <= COMPUTE_UNITS && per_cu > 1 ? 0.6 : 1.0));
+        const double cost = rounds * ((double)kz + warm);
+        if (L.kz == 0 || cost < best) {
+            best = cost;
+            L.kz = kz;
+        }
+    }
+    L.chunks = (int)((nz + L.kz - 1) / L.kz);
+    L.nblocks = (int)(tiles * L.chunks);
+    return L;
+}
+
+// Forward stages: resident workgroups and warm-up per kernel.  FP32 PLM: two
+// 8-wave workgroups per unit, the warm-up (four loads, one z face, the halo)
+// fits 1.5 planes; FP64 PLM one.
+Launch plan_stage(const mhd_ctx *ctx)
+{
+    const bool f32 = ctx->cfg.dtype == MHD_F32, weno = ctx->cfg.limiter == MHD_WENOZ;
+    const int ty = tile_rows_of(f32, weno, ctx->cfg.ndim);
+    if (ctx->cfg.ndim == 3 && !weno) return plan_march(ctx->n[0], ctx->n[1], ctx->n[2], ty, f32 ? 2 : 1, 1.5);
     Launch L;
     L.tiles_x = (int)((ctx->n[0] + TX - 1) / TX);
     L.tiles_y = (int)((ctx->n[1] + ty - 1) / ty);
@@ -112,13 +154,33 @@ Launch plan_stage(const mhd_ctx *ctx, int ty, long long min_blocks = 2048)
     if (ctx->cfg.ndim == 3) {
         // long z chunks amortise the warm-up planes; shorter chunks when
         // the grid would otherwise leave compute units idle.  FP64 WENO-Z
-        // (one 4-wave workgroup per compute unit) starts at 32 planes:
+        // (one workgroup per compute unit) starts at 32 planes:
         // measured 7% faster at 416^3 and 10% with constrained transport at
         // 352^3 than 64; FP32 constrained transport at 16 planes, 2% faster
-        // at 352^3 (FP32 GLM and PLM: no gain)
-        const bool f64 = ctx->cfg.dtype == MHD_F64;
-        kz = (f64 && ctx->cfg.limiter == MHD_WENOZ) ? 32 : ((!f64 && ctx->cfg.ct) ? 16 : 64);
-        while (kz > 4 && tiles * ((ctx->n[2] + kz - 1) / kz) < min_blocks) kz >>= 1;
+        // at 352^3 (FP32 GLM: no gain)
+        kz = !f32 ? 32 : (ctx->cfg.ct ? 16 : 64);
+        while (kz > 4 && tiles * ((ctx->n[2] + kz - 1) / kz) < 2048) kz >>= 1;
+    }
+    L.kz = kz;
+    L.chunks = (int)((ctx->n[2] + kz - 1) / kz);
+    L.nblocks = (int)(tiles * L.chunks);
+    return L;
+}
+
+// Adjoint stages: one workgroup per compute unit; long z chunks, shortened
+// only while the grid has fewer than one workgroup per unit (the warm-up is
+// three planes of z work; one round of longer chunks measured 4% faster at
+// 128^3 than two rounds of half-length ones).
+Launch plan_adjoint(const mhd_ctx *ctx, int ty)
+{
+    Launch L;
+    L.tiles_x = (int)((ctx->n[0] + TX - 1) / TX);
+    L.tiles_y = (int)((ctx->n[1] + ty - 1) / ty);
+    const long long tiles = (long long)L.tiles_x * L.tiles_y;
+    int kz = 1;
+    if (ctx->cfg.ndim == 3) {
+        kz = 64;
+        while (kz > 4 && tiles * ((ctx->n[2] + kz - 1) / kz) < COMPUTE_UNITS) kz >>= 1;
     }
     L.kz = kz;
     L.chunks = (int)((ctx->n[2] + kz - 1) / kz);
@@ -149,7 +211,7 @@ mhd_status launch_step(mhd_ctx *ctx, const T *un, T *unext, T *u1, double dt, do
     const bool rk3 = ctx->cfg.time_order == 3;
     constexpr int TY = tile_rows<T, LIM, NDIM>();
     constexpr int NTH = TX * TY * stage_row_waves<T, LIM>();
-    const Launch L = plan_stage(ctx, TY);
+    const Launch &L = ctx->plan;
     if (L.nblocks > ctx->part_cap) return fail(ctx, MHD_ERR_ARG, "grid too large for partials buffer");
     if (ctx->no_alloc) {
         // the static scratch keeps the last call's flag: this call reports
@@ -229,7 +291,7 @@ mhd_status launch_step_ct(mhd_ctx *ctx, const T *un, T *unext, T *u1, double dt,
     constexpr int TY = tile_rows<T, LIM, 3>();
     constexpr int NTH = TX * TY * stage_row_waves<T, LIM>();
     const bool rk3 = ctx->cfg.time_order == 3;
-    const Launch L = plan_stage(ctx, TY);
+    const Launch &L = ctx->plan;
     StageArgs<T> a;
     a.part = ctx->part;
     a.flag = ctx->flag;
@@ -353,7 +415,7 @@ mhd_status launch_adj_stage(mhd_ctx *ctx, const T *U, const double *lamp, const 
                             double *out, double dt, double ch, double damp)
 {
     constexpr int TY = adj_tile_rows<T, NDIM>();
-    const Launch L = plan_stage(ctx, TY, 256);
+    const Launch L = plan_adjoint(ctx, TY);
     AdjStageArgs<T> a;
     a.U = U;
     a.lamp = lamp;
@@ -392,7 +454,7 @@ mhd_status launch_adjoint(mhd_ctx *ctx, const T *un, const T *u1, const double *
         // recompute the stage-1 state into scratch with the forward kernel
         constexpr int TY = tile_rows<T, LIM, NDIM>();
         constexpr int NTH = TX * TY * stage_row_waves<T, LIM>();
-        const Launch L = plan_stage(ctx, TY);
+        const Launch &L = ctx->plan;
         StageArgs<T> a;
         a.part = ctx->part;
         a.flag = ctx->flag;
@@ -719,12 +781,8 @@ mhd_status mhd_init(const mhd_config *cfg, void *hip_stream, mhd_ctx **out)
     ctx->elem = cfg->dtype == MHD_F32 ? 4 : 8;
     // partials capacity: the forward stage grid (the CFL kernel uses at most
     // CFL_MAX_BLOCKS); the adjoint writes no partials
-    const int ty = cfg->ndim == 1 ? 1
-                 : (cfg->dtype == MHD_F32 ? (cfg->limiter == MHD_WENOZ ? tile_rows<float, LIM_WENOZ, 3>()
-                                                                       : tile_rows<float, LIM_MINMOD, 3>())
-                                          : tile_rows<double, LIM_MINMOD, 3>());
-    const Launch L = plan_stage(ctx, ty);
-    ctx->part_cap = std::max(L.nblocks, CFL_MAX_BLOCKS);
+    ctx->plan = plan_stage(ctx);
+    ctx->part_cap = std::max(ctx->plan.nblocks, CFL_MAX_BLOCKS);
     ctx->ns = cfg->ct ? 12 : NQ;
     hipError_t e = hipMalloc(&ctx->u1_scratch, (size_t)ctx->ns * ctx->ncell * ctx->elem);
     if (e == hipSuccess && cfg->time_order == 3)
@@ -893,8 +951,15 @@ mhd_status mhd_step_noalloc(const mhd_config *cfg, void *hip_stream, const void 
     c.part_cap = NOALLOC_MAX_BLOCKS;
     c.result = (double *)(base + NOALLOC_RESULT_OFF);
     c.flag = (int *)(base + NOALLOC_FLAG_OFF);
-    // launch_step refuses a stage grid beyond NOALLOC_MAX_BLOCKS with
-    // MHD_ERR_ARG before it enqueues anything
+    // the documented limit: 64 x 4 column tiles (FP32 WENO-Z 64 x 8, 1D 64 x
+    // 1) times chunks of up to 64 planes (FP64 WENO-Z 32); the stages' own
+    // grid is never larger
+    const bool f32 = cfg->dtype == MHD_F32, weno = cfg->limiter == MHD_WENOZ;
+    const int rows = cfg->ndim == 1 ? 1 : (f32 && weno ? 8 : 4), planes = !f32 && weno ? 32 : 64;
+    const long long limit_blocks = ((c.n[0] + TX - 1) / TX) * ((c.n[1] + rows - 1) / rows) *
+                                   ((c.n[2] + planes - 1) / planes);
+    if (limit_blocks > NOALLOC_MAX_BLOCKS) return MHD_ERR_ARG;
+    c.plan = plan_stage(&c);
     const mhd_status st = with_scheme(&c, [&](auto sch) {
         using S = decltype(sch);
         return launch_step_nd<typename S::T, S::SOLVER, S::LIM>(&c, Un, U_next, U1_out, dt, c_h, damp);

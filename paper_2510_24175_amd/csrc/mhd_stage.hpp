@@ -9,9 +9,9 @@
 //     the current plane, with an x/y halo of the stencil's half width (2
 //     cells PLM, 3 WENO-Z), sits in LDS;
 //   * z-faces come from a per-lane register window slid along the march
-//     (PLM: V(k), V(k+1) and the limited slope of V(k); WENO-Z: V(k-1) ..
-//     V(k+2) and the upper face value of cell k), so every z-face flux is
-//     computed once per chunk plus one warm-up face;
+//     (PLM: U(k+1) and the limited slope of V(k), with V(k) in LDS; WENO-Z:
+//     V(k-1) .. V(k+2) and the upper face value of cell k), so every z-face
+//     flux is computed once per chunk plus one warm-up face;
 //   * x- and y-faces of the plane are a flat work list of
 //     TY(TX+1) + (TY+1)TX items spread over the workgroup; their fluxes
 //     go through LDS to the cells on both sides, so each face is solved
@@ -156,20 +156,19 @@ __device__ __forceinline__ double wave_max(double v)
     return v;
 }
 
-// Waves per SIMD the kernels are compiled for.  FP32 PLM: 3, a budget of 168
-// registers (stage 1 needs 127, so four 4-wave workgroups share a compute
-// unit; the last stage 165, three).  FP32 WENO-Z: 2 (256 registers; its
-// 8-row workgroups take 155 KB of LDS, one per compute unit).  FP64 PLM: 2
-// (256 registers; the HLLD kernels spill some of them, and still run 11%
-// faster than at one wave per SIMD without spills).  FP64 WENO-Z: 2 (140 KB
-// of LDS, the fluxes laid over the primitive plane, allows one workgroup per
-// compute unit: 4 rows with two waves each, the helper waves below; 256
-// registers, some spilled: the 416^3 SSP-RK3 step ran 14% faster than with
-// one 4-wave workgroup at 512 registers, before the last stage's reductions
-// moved to the helpers).
-template <typename T, int LIM> constexpr int stage_min_waves()
+// Waves per SIMD the kernels are compiled for.  FP32 PLM in 8-row tiles: 4, a
+// budget of 128 registers (the first stage needs 106, the last 128), two
+// 8-wave workgroups per compute unit; a spilled register in the plane loop
+// costs more than the wave it buys (a last stage with 21 spilled: 8.3 ms at
+// 512^3 against 5.8 without).  FP32 PLM in 2D: 3.  FP32 WENO-Z: 2 (256
+// registers; its 8-row workgroups take 155 KB of LDS, one per compute unit).
+// FP64 PLM: 2 (256 registers, none spilled; one 8-wave workgroup of 154 KB per
+// compute unit).  FP64 WENO-Z: 2 (140 KB of LDS, the fluxes laid over the
+// primitive plane, allows one workgroup per compute unit: 4 rows with two
+// waves each, the helper waves below).
+template <typename T, int LIM, int TY> constexpr int stage_min_waves()
 {
-    return sizeof(T) == 4 ? (LIM == LIM_WENOZ ? 2 : 3) : 2;
+    return sizeof(T) == 4 ? (LIM == LIM_WENOZ ? 2 : (TY == 8 ? 4 : 3)) : 2;
 }
 
 // Waves per tile row.  FP64 WENO-Z's arrays leave room for one workgroup per
@@ -191,7 +190,7 @@ template <typename T, int LIM> constexpr int stage_row_waves()
 constexpr bool last_stage(int kind) { return kind == 2 || kind == 4; }
 
 template <typename T, int SOLVER, int LIM, int NDIM, int KIND, int TY, bool CT = false>
-__global__ void __launch_bounds__(TX *TY *(stage_row_waves<T, LIM>()), (stage_min_waves<T, LIM>()))
+__global__ void __launch_bounds__(TX *TY *(stage_row_waves<T, LIM>()), (stage_min_waves<T, LIM, TY>()))
 stage_kernel(const StageArgs<T> a)
 {
     constexpr bool WENO = LIM == LIM_WENOZ;
@@ -243,7 +242,10 @@ stage_kernel(const StageArgs<T> a)
     constexpr bool HELP_RED = LAST && stage_row_waves<T, LIM>() > 1;
     static_assert(!HELP_RED || sizeof(T) == 8, "helper reductions keep FP64 sums in T registers");
     constexpr int OOUT = SZL0;
-    constexpr int SZL = OOUT + (HELP_RED ? NQ * TY * TX : 0);
+    // PLM in 8-row tiles: two workgroups leave room for the momentum and
+    // energy of U(k) (ME), four registers that the last stage lacks
+    constexpr bool ME_LDS = !WENO && NDIM == 3 && TY == 8;
+    constexpr int SZL = OOUT + (HELP_RED ? NQ * TY * TX : 0) + (ME_LDS ? 4 * TY * TX : 0);
     static_assert(SZL * (int)sizeof(T) <= 160 * 1024, "LDS of one compute unit");
 
     __shared__ T lds[SZL];
@@ -260,20 +262,14 @@ stage_kernel(const StageArgs<T> a)
     T *const EX = lds + OEX;
     T *const EY = lds + OEY;
     T *const OUTS = lds + OOUT;
+    T *const ME = lds + OOUT;
 
     const int t = threadIdx.x;
     const int tx = t & (TX - 1);
     const int ty = t / TX;  // tile row of a column owner (>= TY: helper)
     const int wave = __builtin_amdgcn_readfirstlane(ty);
-    // With one wave per tile row every wave owns its row.  For the 3D FP32
-    // kernels the owner test is folded at compile time: the compiler then
-    // holds the PLM stages to 127 and 165 registers (four and three
-    // workgroups per compute unit) instead of 138 and 168 with 8 spilled, and
-    // the WENO-Z stages (one workgroup per unit either way) run 1-4% faster.
-    // Elsewhere it is left to run time, which the compiler's allocation
-    // favours (FP64 PLM: 0 and 24 spilled registers against 28 and 87; 2D
-    // FP32 PLM: 127 against 129, a workgroup per compute unit more).
-    constexpr bool ALL_OWN = stage_row_waves<T, LIM>() == 1 && sizeof(T) == 4 && NDIM == 3;
+    // With one wave per tile row every wave owns its row.
+    constexpr bool ALL_OWN = stage_row_waves<T, LIM>() == 1;
     const bool owner = ALL_OWN || wave < TY;  // wave-uniform
     const int lb = logical_block(blockIdx.x, a.nblocks);
     const int tile_x = lb % a.tiles_x;
@@ -328,22 +324,33 @@ stage_kernel(const StageArgs<T> a)
         load_cell(a.uin, a.ncell, c, u);
         ok &= cons_to_prim(u, a.ph, v);
     };
+    // the same, keeping the conserved momentum and energy
+    auto prim_at_keep = [&](long long c, T *v, T *me) {
+        T u[NQ];
+        load_cell(a.uin, a.ncell, c, u);
+        ok &= cons_to_prim(u, a.ph, v);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) me[q] = u[MX + q];
+    };
     auto slope9 = [&](const T *vm, const T *v0, const T *vp, T *s) {
 #pragma unroll
         for (int q = 0; q < NQ; ++q) s[q] = limited_slope<LIM>(v0[q] - vm[q], vp[q] - v0[q]);
     };
 
-    // Flux through one face of the plane from its two states, stored in LDS.
-    // Constrained transport: fc is the cell
-    // whose lower face this is (its face value is the normal field) and, for
-    // the tile's own faces (mine), the two transverse field fluxes go to flx.
-    auto flux_item = [&](auto dir, const T *VL, const T *VR, T *dst, int fstride, long long fc,
-                         bool mine) {
+    // Flux through one face of the plane (offset zk) from its two states,
+    // stored in LDS.  (x, y) is the tile cell whose lower face this is.
+    // Constrained transport: its face value is the normal field and, for the
+    // tile's own faces (mine) of grid cells, the two transverse field fluxes
+    // go to flx.
+    auto flux_item = [&](auto dir, const T *VL, const T *VR, T *dst, int fstride, long long zk, int x,
+                         int y, bool mine) {
         constexpr int D = decltype(dir)::value;
         T F[NQ];
         if constexpr (CT) {
+            const long long fc = zk + (long long)remap_index(j0 + y, a.ny, a.per[1]) * a.nx +
+                                 remap_index(i0 + x, a.nx, a.per[0]);
             face_flux<T, SOLVER, true>(VL, VR, D, a.ph, F, a.uin[(9 + D) * a.ncell + fc]);
-            if (mine && a.flx) {
+            if (mine && (i0 + x < a.nx) & (j0 + y < a.ny) && a.flx) {
                 a.flx[(2 * D) * a.ncell + fc] = F[D == 0 ? BY : BX];
                 a.flx[(2 * D + 1) * a.ncell + fc] = F[BZ];
             }
@@ -353,16 +360,10 @@ stage_kernel(const StageArgs<T> a)
 #pragma unroll
         for (int q = 0; q < NQ; ++q) dst[q * fstride] = F[q];
     };
-    // owner cell (in plane zk) of the lower face of tile cell (x, y), and
-    // whether that cell is in the grid
-    auto face_cell = [&](long long zk, int x, int y) -> long long {
-        return zk + (long long)remap_index(j0 + y, a.ny, a.per[1]) * a.nx + remap_index(i0 + x, a.nx, a.per[0]);
-    };
-    auto in_grid = [&](int x, int y) -> bool { return (i0 + x < a.nx) & (j0 + y < a.ny); };
     // PLM face from the LDS stencil w0..w3 (stride apart; the face lies
     // between w1 and w2): limited slopes of w1 and w2, face states, flux.
-    auto face_item = [&](auto dir, const T *base, int stride, T *dst, int fstride, long long fc,
-                         bool mine) {
+    auto face_item = [&](auto dir, const T *base, int stride, T *dst, int fstride, long long zk, int x,
+                         int y, bool mine) {
         T VL[NQ], VR[NQ];
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
@@ -373,15 +374,17 @@ stage_kernel(const StageArgs<T> a)
             VL[q] = w1 + T(0.5) * s1;
             VR[q] = w2 - T(0.5) * s2;
         }
-        flux_item(dir, VL, VR, dst, fstride, fc, mine);
+        flux_item(dir, VL, VR, dst, fstride, zk, x, y, mine);
     };
 
-    // z window.  PLM: V(k), V(k+1) and the limited slope of V(k).  WENO-Z:
-    // V(k-1) .. V(k+2) and ZT, the upper face value of cell k.  Fzm is the
-    // flux through face k-1/2.
-    constexpr int ZW = WENO ? 4 : 2;
-    constexpr int ZC = WENO ? 1 : 0;       // window slot of plane k
-    T Wz[ZW][NQ], D0[NQ], ZT[NQ], Fzm[NQ];
+    // z window.  PLM: the conserved U(k+1), the limited slope D0 of V(k) and the
+    // momentum and energy of U(k); V(k) itself is the own cell of the LDS
+    // plane, and density, field and psi are the same in U and V, so the
+    // combine needs no second read of the state.  WENO-Z: V(k-1) .. V(k+2) and
+    // ZT, the upper face value of cell k.  Fzm is the flux through face k-1/2.
+    constexpr int ZW = WENO ? 4 : 1;
+    constexpr int ZC = WENO ? 1 : 0;       // window slot of plane k (WENO-Z)
+    T Wz[ZW][NQ], D0[NQ], ZT[NQ], Fzm[NQ], me0[4], un1[NQ];
     // A helper wave keeps its running FP64 sums of the cells its row's owner
     // left in OUTS (same column) in Fzm and its maxima of the signal speeds
     // in ZT[0..1]: registers the owners hold through the march anyway and
@@ -423,25 +426,37 @@ stage_kernel(const StageArgs<T> a)
                 wenoz_pair(Vm2[q], Wz[0][q], Wz[1][q], Wz[2][q], Wz[3][q], ZT[q], VR[q]);
             }
         } else {
-            T Vm2[NQ], Vm1[NQ], Dm1[NQ];
+            T Vm2[NQ], Vm1[NQ], V0[NQ], Dm1[NQ];
             prim_at(zoff(k0 - 2) + own, Vm2);
             prim_at(zoff(k0 - 1) + own, Vm1);
-            prim_at(zoff(k0) + own, Wz[0]);
-            prim_at(zoff(k0 + 1) + own, Wz[1]);
-            slope9(Vm2, Vm1, Wz[0], Dm1);
-            slope9(Vm1, Wz[0], Wz[1], D0);
+            prim_at_keep(zoff(k0) + own, V0, me0);
+            load_cell(a.uin, a.ncell, zoff(k0 + 1) + own, un1);
+            T V1[NQ];
+            ok &= cons_to_prim(un1, a.ph, V1);
+            slope9(Vm2, Vm1, V0, Dm1);
+            slope9(Vm1, V0, V1, D0);
+            if (ME_LDS) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) ME[q * TY * TX + t] = me0[q];
+            }
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
                 VL[q] = Vm1[q] + T(0.5) * Dm1[q];
-                VR[q] = Wz[0][q] - T(0.5) * D0[q];
+                VR[q] = V0[q] - T(0.5) * D0[q];
+                P[q * PLANE + own_slot] = V0[q];
             }
         }
         if constexpr (CT)
             face_flux<T, SOLVER, true>(VL, VR, 2, a.ph, Fzm, a.uin[11 * a.ncell + zoff(k0) + own]);
         else
             face_flux<T, SOLVER>(VL, VR, 2, a.ph, Fzm);
-    } else if (owner) {
-        prim_at(own, Wz[ZC]);
+    } else if constexpr (WENO) {
+        if (owner) prim_at(own, Wz[ZC]);
+    } else {
+        T V0[NQ];
+        prim_at_keep(own, V0, me0);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) P[q * PLANE + own_slot] = V0[q];
     }
 
     double smax = 0.0, cmax = 0.0;
@@ -453,56 +468,212 @@ stage_kernel(const StageArgs<T> a)
 #pragma unroll
     for (int q = 0; q < (HELP_RED ? 1 : NQ); ++q) sum[q] = 0.0;
 
-    // The stage combine's inputs at the thread's own cell are loaded at the
-    // top of the plane, so that their latency hides behind the face phases,
-    // where registers allow: FP32 PLM (measured 2% faster).  FP64 PLM would
-    // spill (25% slower), FP32 WENO-Z runs at two waves per SIMD (3% slower),
-    // and FP64 WENO-Z with its helper waves spills 2.2x more (the 416^3 step
-    // 55% slower); those load them at the update.
-    constexpr bool PREFETCH = (sizeof(T) == 4) && !WENO;
-    auto load_combine = [&](long long c, T *cin, T *cun) {
+    // divergence and stage combine of the own cell of plane k from its
+    // conserved input state cin, the plane's x and y fluxes in LDS and the z
+    // fluxes Fzm and Fzp
+    auto update = [&](int k, long long c, const T *cin, const T *cun, const T *Fzp) {
+        T L[NQ];
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            cin[q] = a.uin[q * a.ncell + c];
-            cun[q] = KIND == 1 ? T(0) : a.un[q * a.ncell + c];
+            const T *fx = &FXs[q * TY * (TX + 1) + ty * (TX + 1) + tx];
+            T l = (fx[0] - fx[1]) * a.idx[0];
+            if (NDIM >= 2) {
+                const T *fy = &FYs[q * (TY + 1) * TX + ty * TX + tx];
+                l += (fy[0] - fy[TX]) * a.idx[1];
+            }
+            if (NDIM == 3) l += (Fzm[q] - Fzp[q]) * a.idx[2];
+            L[q] = l;
+        }
+        T out[NQ];
+        if (KIND == 1) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) out[q] = cin[q] + a.dt * L[q];
+        } else if (KIND == 2) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) out[q] = T(0.5) * ((cun[q] + cin[q]) + a.dt * L[q]);
+        } else if (KIND == 3) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) out[q] = T(0.75) * cun[q] + T(0.25) * (cin[q] + a.dt * L[q]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) out[q] = cun[q] * T(1.0 / 3.0) + T(2.0 / 3.0) * (cin[q] + a.dt * L[q]);
+        }
+        if (LAST) out[PSI] *= a.damp;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            // constrained transport: the face update writes the cell field
+            if (CT && q >= BX && q <= BZ) continue;
+            __builtin_nontemporal_store(out[q], &a.uout[q * a.ncell + c]);  // not read again here
+        }
+        if (CT && a.flx) {
+            // transverse field fluxes of this cell's lower z face
+            a.flx[4 * a.ncell + c] = Fzm[BX];
+            a.flx[5 * a.ncell + c] = Fzm[BY];
+        }
+        if constexpr (HELP_RED) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) OUTS[q * TY * TX + t] = out[q];
+        } else if (LAST) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) sum[q] += (double)out[q];
+            if constexpr (sizeof(T) == 8) {
+                ok &= cell_speeds<T, NDIM>(out, a.gamma_d, a.idx_d, smax, cmax);
+            } else {
+                float ls, lc;
+                ok &= cell_speeds_f32<NDIM>(out, a.ph.gamma, a.idx, ls, lc);
+                k_s = ls > best_s ? k : k_s;
+                best_s = __builtin_fmaxf(best_s, ls);
+                k_c = lc > best_c ? k : k_c;
+                best_c = __builtin_fmaxf(best_c, lc);
+            }
         }
     };
 
-    for (int k = k0; k < k1; ++k) {
-        const long long zk = zoff(k);
-        T cin[NQ], cun[NQ];
-        if (PREFETCH && active) load_combine(zk + own, cin, cun);
-        // the fluxes of the previous plane sit where P goes; the helpers
-        // read the previous plane's results
-        if ((ALIAS || HELP_RED) && k > k0) __syncthreads();
-        // (a) primitives of plane k into LDS: own column and halo cell
-        if (owner) {
+    // PLM.  Per plane: the x and y faces from the LDS plane, then the z face,
+    // the update and the next plane's primitives.  The own cells of plane k+2
+    // are loaded before the x and y faces and used after them, so that their
+    // latency hides behind the faces; FP32 also loads the halo cells of plane
+    // k+1 and Un before the z face (FP64 lacks the registers).  Each cell is
+    // read once as an own cell and once per halo that holds it: 512^3 FP32
+    // fetches 7.9 GB in the first stage (4.8 compulsory) against 11.8 when the
+    // combine re-read the state, and the stages take 3.83 + 4.55 ms against
+    // 4.30 + 5.42 with the z face first, the re-read and 4-row tiles (256^3
+    // FP64 1.22 + 1.45 against 1.37 + 1.64).  About 70% of the time is VALU
+    // issue (3.2 face rounds of ~270 instructions per 64 cells), the rest
+    // waits for LDS, barriers and memory.
+    if constexpr (!WENO) {
+        constexpr bool EARLY = sizeof(T) == 4;
+        auto load_halo = [&](long long z, T (*h)[NQ]) {
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) P[q * PLANE + own_slot] = Wz[ZC][q];
-        }
+            for (int m = 0; m < HPT; ++m)
+                if (t + m * NT < NH) load_cell(a.uin, a.ncell, z + h_off[m], h[m]);
+        };
+        auto put_halo = [&](T (*h)[NQ]) {
 #pragma unroll
-        for (int m = 0; m < HPT; ++m) {
-            if (t + m * NT < NH) {
-                T hv[NQ];
-                prim_at(zk + h_off[m], hv);
+            for (int m = 0; m < HPT; ++m) {
+                if (t + m * NT < NH) {
+                    T hv[NQ];
+                    ok &= cons_to_prim(h[m], a.ph, hv);
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) P[q * PLANE + h_slot[m]] = hv[q];
+                    for (int q = 0; q < NQ; ++q) P[q * PLANE + h_slot[m]] = hv[q];
+                }
+            }
+        };
+        T hu[HPT][NQ];
+        load_halo(zoff(k0), hu);
+        put_halo(hu);
+        __syncthreads();
+        for (int k = k0; k < k1; ++k) {
+            const long long c = zoff(k) + own;
+            T un2[NQ];
+            if (NDIM == 3) load_cell(a.uin, a.ncell, zoff(k + 2) + own, un2);
+            // x and y faces of the plane.  Items go out in 64-wide chunks, one
+            // chunk per wave at a time; x items are padded to whole chunks so
+            // every chunk is a single direction and the solver is inlined with
+            // a compile-time frame.
+            for (int ch = wave; ch < NCHUNK; ch += NW) {
+                if (ch < NCHX) {
+                    // lanes past the last item repeat it (same values, same slot)
+                    const int it = min(ch * TX + tx, NFX - 1);
+                    const int r = it / (TX + 1), f = it - r * (TX + 1);
+                    // cells f-2 .. f+1 of row r
+                    face_item(std::integral_constant<int, 0>{}, &P[(r + HY) * PX + f], 1, &FXs[it],
+                              TY * (TX + 1), zoff(k), f, r, f < TX);
+                } else {
+                    const int it = (ch - NCHX) * TX + tx;
+                    const int r = it / TX, f = it - r * TX;
+                    // rows r-2 .. r+1 of column f
+                    face_item(std::integral_constant<int, 1>{}, &P[r * PX + f + H], PX, &FYs[it],
+                              (TY + 1) * TX, zoff(k), f, r, r < TY);
+                }
+            }
+            __syncthreads();
+            if (EARLY && k + 1 < k1) load_halo(zoff(k + 1), hu);
+            T V0[NQ], V1[NQ], D1[NQ], Fzp[NQ], cun[NQ];
+            if (EARLY && KIND != 1) load_cell(a.un, a.ncell, c, cun);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) V0[q] = P[q * PLANE + own_slot];
+            if (NDIM == 3) {
+                T V2[NQ], VL[NQ], VR[NQ];
+                cons_to_prim(un1, a.ph, V1);
+                ok &= cons_to_prim(un2, a.ph, V2);
+                slope9(V0, V1, V2, D1);
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    VL[q] = V0[q] + T(0.5) * D0[q];
+                    VR[q] = V1[q] - T(0.5) * D1[q];
+                }
+                if constexpr (CT)
+                    face_flux<T, SOLVER, true>(VL, VR, 2, a.ph, Fzp, a.uin[11 * a.ncell + zoff(k + 1) + own]);
+                else
+                    face_flux<T, SOLVER>(VL, VR, 2, a.ph, Fzp);
+            }
+            if (active) {
+                if (!EARLY && KIND != 1) load_cell(a.un, a.ncell, c, cun);
+                if (ME_LDS) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) me0[q] = ME[q * TY * TX + t];
+                }
+                const T cin[NQ] = {V0[RHO], me0[0], me0[1], me0[2], me0[3], V0[BX], V0[BY], V0[BZ], V0[PSI]};
+                update(k, c, cin, cun, Fzp);
+            }
+            if (NDIM == 3) {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    P[q * PLANE + own_slot] = V1[q];
+                    D0[q] = D1[q];
+                    Fzm[q] = Fzp[q];
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (ME_LDS) ME[q * TY * TX + t] = un1[MX + q];
+                    else me0[q] = un1[MX + q];
+                }
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) un1[q] = un2[q];
+                if (k + 1 < k1) {
+                    if (!EARLY) load_halo(zoff(k + 1), hu);
+                    put_halo(hu);
+                }
+                __syncthreads();
             }
         }
-        if constexpr (OVERLAP) {
-            // the plane is in LDS: the reconstructions may start
-            if (t == 0) chunk_next = 0;
-            __syncthreads();
-        }
-        // (the previous plane's results stay until this plane's update,
-        // several barriers on)
-        if (HELP_RED && !owner && k > k0) helper_fold();
-        // (b) z-face k+1/2 from the register window
-        T Fzp[NQ], D1[NQ];
-        if (NDIM == 3 && owner) {
-            T Vn[NQ], VL[NQ], VR[NQ];
-            prim_at(zoff(k + ZW - ZC) + own, Vn);  // PLM: V(k+2); WENO-Z: V(k+3)
-            if constexpr (WENO) {
+    }
+
+    // WENO-Z
+    if constexpr (WENO) {
+        for (int k = k0; k < k1; ++k) {
+            const long long zk = zoff(k);
+            // the fluxes of the previous plane sit where P goes; the helpers
+            // read the previous plane's results
+            if ((ALIAS || HELP_RED) && k > k0) __syncthreads();
+            // (a) primitives of plane k into LDS: own column and halo cell
+            if (owner) {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) P[q * PLANE + own_slot] = Wz[ZC][q];
+            }
+#pragma unroll
+            for (int m = 0; m < HPT; ++m) {
+                if (t + m * NT < NH) {
+                    T hv[NQ];
+                    prim_at(zk + h_off[m], hv);
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) P[q * PLANE + h_slot[m]] = hv[q];
+                }
+            }
+            if constexpr (OVERLAP) {
+                // the plane is in LDS: the reconstructions may start
+                if (t == 0) chunk_next = 0;
+                __syncthreads();
+            }
+            // (the previous plane's results stay until this plane's update,
+            // several barriers on)
+            if (HELP_RED && !owner && k > k0) helper_fold();
+            // (b) z-face k+1/2 from the register window
+            T Fzp[NQ];
+            if (NDIM == 3 && owner) {
+                T Vn[NQ], VL[NQ], VR[NQ];
+                prim_at(zoff(k + ZW - ZC) + own, Vn);  // V(k+3)
                 // cell k+1: its lower face value closes face k+1/2, its upper
                 // one is carried to the next plane
 #pragma unroll
@@ -510,34 +681,25 @@ stage_kernel(const StageArgs<T> a)
                     VL[q] = ZT[q];
                     wenoz_pair(Wz[0][q], Wz[1][q], Wz[2][q], Wz[3][q], Vn[q], ZT[q], VR[q]);
                 }
-            } else {
-                slope9(Wz[0], Wz[1], Vn, D1);
+                if constexpr (CT)
+                    face_flux<T, SOLVER, true>(VL, VR, 2, a.ph, Fzp, a.uin[11 * a.ncell + zoff(k + 1) + own]);
+                else
+                    face_flux<T, SOLVER>(VL, VR, 2, a.ph, Fzp);
+                // The flux is used after the x/y faces: without a use here the
+                // compiler moves half of the z face past them and keeps its
+                // intermediates (about 40 registers) live across them.
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) {
-                    VL[q] = Wz[0][q] + T(0.5) * D0[q];
-                    VR[q] = Wz[1][q] - T(0.5) * D1[q];
+                for (int q = 0; q < NQ; ++q) asm volatile("" : "+v"(Fzp[q]));
+                // slide the window by one plane
+#pragma unroll
+                for (int m = 0; m + 1 < ZW; ++m) {
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) Wz[m][q] = Wz[m + 1][q];
                 }
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) Wz[ZW - 1][q] = Vn[q];
             }
-            if constexpr (CT)
-                face_flux<T, SOLVER, true>(VL, VR, 2, a.ph, Fzp, a.uin[11 * a.ncell + zoff(k + 1) + own]);
-            else
-                face_flux<T, SOLVER>(VL, VR, 2, a.ph, Fzp);
-            // The flux is used after the x/y faces: without a use here the
-            // compiler moves half of the z face past them and keeps its
-            // intermediates (about 40 registers) live across them.
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) asm volatile("" : "+v"(Fzp[q]));
-            // slide the window by one plane
-#pragma unroll
-            for (int m = 0; m + 1 < ZW; ++m) {
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) Wz[m][q] = Wz[m + 1][q];
-            }
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) Wz[ZW - 1][q] = Vn[q];
-        }
-        if constexpr (!OVERLAP) __syncthreads();
-        if constexpr (WENO) {
+            if constexpr (!OVERLAP) __syncthreads();
             // (c0) WENO-Z face values of every cell the plane's faces need,
             // each from the five cells centred on it: x items for cells
             // -1 .. TX of each row, y items for rows -1 .. TY of each column.
@@ -598,8 +760,7 @@ stage_kernel(const StageArgs<T> a)
                         VL[q] = EX[q * QS + r * NXE + f];
                         VR[q] = EX[NQ * QS + q * QS + r * NXE + f + 1];
                     }
-                    flux_item(std::integral_constant<int, 0>{}, VL, VR, &FXs[it], TY * (TX + 1),
-                              face_cell(zk, f, r), f < TX && in_grid(f, r));
+                    flux_item(std::integral_constant<int, 0>{}, VL, VR, &FXs[it], TY * (TX + 1), zk, f, r, f < TX);
                 } else {
                     const int it = (ch - NCHX) * TX + tx;
                     const int r = it / TX, c = it - r * TX;
@@ -609,98 +770,22 @@ stage_kernel(const StageArgs<T> a)
                         VL[q] = EY[q * QS + r * TX + c];
                         VR[q] = EY[NQ * QS + q * QS + (r + 1) * TX + c];
                     }
-                    flux_item(std::integral_constant<int, 1>{}, VL, VR, &FYs[r * TX + c], (TY + 1) * TX,
-                              face_cell(zk, c, r), r < TY && in_grid(c, r));
+                    flux_item(std::integral_constant<int, 1>{}, VL, VR, &FYs[it], (TY + 1) * TX, zk, c, r, r < TY);
                 }
             }
-        } else {
-            // (c) x- and y-faces of the plane.  Items go out in 64-wide chunks,
-            // one chunk per wave at a time; x items are padded to whole chunks so
-            // every chunk is a single direction and the solver is inlined with a
-            // compile-time frame.
-            for (int ch = wave; ch < NCHUNK; ch += NW) {
-                if (ch < NCHX) {
-                    // lanes past the last item repeat it (same values, same slot)
-                    const int it = min(ch * TX + tx, NFX - 1);
-                    const int r = it / (TX + 1), f = it - r * (TX + 1);
-                    // cells f-2 .. f+1 of row r
-                    face_item(std::integral_constant<int, 0>{}, &P[(r + HY) * PX + f], 1, &FXs[it],
-                              TY * (TX + 1), face_cell(zk, f, r), f < TX && in_grid(f, r));
-                } else {
-                    const int it = (ch - NCHX) * TX + tx;
-                    const int r = it / TX, c = it - r * TX;
-                    // rows r-2 .. r+1 of column c
-                    face_item(std::integral_constant<int, 1>{}, &P[r * PX + c + H], PX, &FYs[r * TX + c],
-                              (TY + 1) * TX, face_cell(zk, c, r), r < TY && in_grid(c, r));
-                }
+            __syncthreads();
+            // (d) divergence and stage combine (the combine's inputs loaded here:
+            // earlier loads spill in FP64 and measured 3% slower in FP32)
+            if (active) {
+                const long long c = zk + own;
+                T cin[NQ], cun[NQ];
+                load_cell(a.uin, a.ncell, c, cin);
+                if (KIND != 1) load_cell(a.un, a.ncell, c, cun);
+                update(k, c, cin, cun, Fzp);
             }
-        }
-        __syncthreads();
-        // (d) divergence and stage combine
-        if (active) {
-            const long long c = zk + own;
-            T L[NQ];
+            if (NDIM == 3 && owner) {
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const T *fx = &FXs[q * TY * (TX + 1) + ty * (TX + 1) + tx];
-                T l = (fx[0] - fx[1]) * a.idx[0];
-                if (NDIM >= 2) {
-                    const T *fy = &FYs[q * (TY + 1) * TX + ty * TX + tx];
-                    l += (fy[0] - fy[TX]) * a.idx[1];
-                }
-                if (NDIM == 3) l += (Fzm[q] - Fzp[q]) * a.idx[2];
-                L[q] = l;
-            }
-            if (!PREFETCH) load_combine(c, cin, cun);
-            T out[NQ];
-            if (KIND == 1) {
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) out[q] = cin[q] + a.dt * L[q];
-            } else if (KIND == 2) {
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) out[q] = T(0.5) * ((cun[q] + cin[q]) + a.dt * L[q]);
-            } else if (KIND == 3) {
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) out[q] = T(0.75) * cun[q] + T(0.25) * (cin[q] + a.dt * L[q]);
-            } else {
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) out[q] = cun[q] * T(1.0 / 3.0) + T(2.0 / 3.0) * (cin[q] + a.dt * L[q]);
-            }
-            if (LAST) out[PSI] *= a.damp;
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                // constrained transport: the face update writes the cell field
-                if (CT && q >= BX && q <= BZ) continue;
-                __builtin_nontemporal_store(out[q], &a.uout[q * a.ncell + c]);  // not read again here
-            }
-            if (CT && a.flx) {
-                // transverse field fluxes of this cell's lower z face
-                a.flx[4 * a.ncell + c] = Fzm[BX];
-                a.flx[5 * a.ncell + c] = Fzm[BY];
-            }
-            if constexpr (HELP_RED) {
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) OUTS[q * TY * TX + t] = out[q];
-            } else if (LAST) {
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) sum[q] += (double)out[q];
-                if constexpr (sizeof(T) == 8) {
-                    ok &= cell_speeds<T, NDIM>(out, a.gamma_d, a.idx_d, smax, cmax);
-                } else {
-                    float ls, lc;
-                    ok &= cell_speeds_f32<NDIM>(out, a.ph.gamma, a.idx, ls, lc);
-                    k_s = ls > best_s ? k : k_s;
-                    best_s = __builtin_fmaxf(best_s, ls);
-                    k_c = lc > best_c ? k : k_c;
-                    best_c = __builtin_fmaxf(best_c, lc);
-                }
-            }
-        }
-        if (NDIM == 3 && owner) {
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                Fzm[q] = Fzp[q];
-                if constexpr (!WENO) D0[q] = D1[q];
+                for (int q = 0; q < NQ; ++q) Fzm[q] = Fzp[q];
             }
         }
     }
