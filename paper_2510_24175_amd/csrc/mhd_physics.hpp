@@ -42,52 +42,40 @@ template <> struct Num<float> {
 };
 
 template <> struct Num<double> {
-    // reciprocal: the hardware estimate (relative error up to 2^-24.4)
-    // refined by two Newton-Raphson steps (e = 1 - x r, r <- r + r e); equal
-    // to the IEEE quotient on every one of 2M log-uniform samples in
-    // [1e-300, 1e300] (one step leaves up to 11 ulps)
+    // reciprocal: the hardware estimate y (relative error up to 2^-24.1) with
+    // a third-order correction, y (1 + e + e^2) with e = 1 - x y exact; the
+    // IEEE quotient on all but 529 of 2M samples in [1e-297, 1e297], within
+    // half an ulp on every one, as two Newton steps (one operation more)
     static __device__ __forceinline__ double rcp(double x)
     {
-        double r = __builtin_amdgcn_rcp(x);
-        double e = __builtin_fma(-x, r, 1.0);
-        r = __builtin_fma(r, e, r);
-        e = __builtin_fma(-x, r, 1.0);
-        return __builtin_fma(r, e, r);
+        const double y = __builtin_amdgcn_rcp(x);
+        const double e = __builtin_fma(-x, y, 1.0);
+        return __builtin_fma(y, __builtin_fma(e, e, e), y);
     }
-    // square root: Goldschmidt's coupled iteration from the hardware
-    // reciprocal-square-root estimate y ~ 1/sqrt(x) (g = x y -> sqrt(x),
-    // h = y/2 -> 1/(2 sqrt(x)), r = 1/2 - g h), then two residual corrections
-    // g <- g + (x - g^2) h.  Bitwise the IEEE square root on every one of 4M
-    // log-uniform samples in [1e-300, 1e300]; below that the residuals lose
-    // bits in subnormal products (the kernels' roots are of sums with normal
-    // terms).  x + DBL_MIN keeps the estimate finite at x = 0 (result 0);
-    // negative x gives NaN.  Ten instructions against about seventeen for
-    // the library's scaled sequence.
+    // square root: one Goldschmidt step from the hardware reciprocal-square-root
+    // estimate y ~ 1/sqrt(x) (g = x y -> sqrt(x), h = y/2, r = 1/2 - g h: g is then
+    // within 2^-47) and one residual correction g <- g + (x - g^2) h, whose
+    // error is h's 2^-24 of 2^-47.  The IEEE root on all but 513 of 2M samples
+    // in [1e-297, 1e297], within half an ulp on every one, as with h refined
+    // and a second correction (three operations more).  x + DBL_MIN keeps the
+    // estimate finite at x = 0 (result 0); negative x gives NaN; subnormal
+    // results lose bits (the kernels' roots are of sums with normal terms).
     static __device__ __forceinline__ double sqrt(double x)
     {
         const double y = __builtin_amdgcn_rsq(x + 2.2250738585072014e-308);
-        double g = x * y, h = 0.5 * y;
-        const double r = __builtin_fma(-g, h, 0.5);
-        g = __builtin_fma(g, r, g);
-        h = __builtin_fma(h, r, h);
-        double d = __builtin_fma(-g, g, x);
-        g = __builtin_fma(d, h, g);
-        d = __builtin_fma(-g, g, x);
-        return __builtin_fma(d, h, g);
+        double g = x * y;
+        const double h = 0.5 * y;
+        g = __builtin_fma(g, __builtin_fma(-g, h, 0.5), g);
+        return __builtin_fma(__builtin_fma(-g, g, x), h, g);
     }
-    // reciprocal square root: two steps of the same coupled iteration,
-    // 1/sqrt(x) = 2h, within 2 ulps for normal x > 0 (NaN at 0, as the
-    // refined reciprocal of a zero root)
+    // reciprocal square root: y (1 + e/2 + 3/8 e^2), e = 1 - x y^2; within 1.0
+    // ulp for normal x > 0 (two Goldschmidt steps: 1.64, three operations
+    // more); NaN at 0
     static __device__ __forceinline__ double rsqrt(double x)
     {
         const double y = __builtin_amdgcn_rsq(x);
-        double g = x * y, h = 0.5 * y;
-        double r = __builtin_fma(-g, h, 0.5);
-        g = __builtin_fma(g, r, g);
-        h = __builtin_fma(h, r, h);
-        r = __builtin_fma(-g, h, 0.5);
-        h = __builtin_fma(h, r, h);
-        return 2.0 * h;
+        const double e = __builtin_fma(-(x * y), y, 1.0);
+        return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
     }
     static __device__ __forceinline__ double abs(double x) { return __builtin_fabs(x); }
     static __device__ __forceinline__ double min(double a, double b) { return __builtin_fmin(a, b); }
@@ -229,77 +217,60 @@ template <int LIM, typename T> __device__ __forceinline__ T limited_slope(T a, T
 // (1, 6, 3)/10 on (S0, S1, S2) for the right face and (3, 6, 1)/10 for the
 // left, each scaled by 1 + tau5 / (beta_k + eps).
 //
-// FP64: the weights are multiplied through by (beta0+eps)(beta1+eps)(beta2+eps),
+// The weights are multiplied through by (beta0+eps)(beta1+eps)(beta2+eps),
 // W_k = prod_{j != k}(beta_j + eps) (beta_k + eps + tau5) (formed as the triple product
-// plus tau5 times the pair product), the linear weights
-// are folded into the candidate deviations and the weight sums, and both faces
-// are normalised with one reciprocal of the product of the two weight sums,
-// the Newton-refined one (within an ulp).  That product lies between eps^6 and
-// about 4 beta_max^6, so it and its reciprocal stay normal for indicators
-// between eps and 1e51 (differences of a few 1e25 between neighbouring cell
-// values).  FP32: the reciprocals are the hardware
-// approximation and the ratio tau5/(beta_k + eps) is capped at 1e18 so that
-// the weights stay finite for jumps whose indicators exceed FLT_MAX * eps; the
-// cap only binds where two candidates are both 1e18 times smoother than
-// tau5, and then their face values agree far below FP32 resolution.
+// plus tau5 times the pair product), and the linear weights are folded into
+// the candidate deviations and the weight sums.  FP64 normalises both faces
+// with one reciprocal of the product of the two weight sums: it lies between
+// (4 eps)^6 and about 4 (4 beta_max)^6, so it and its reciprocal stay normal for
+// indicators between eps and 2e50 (differences of 1e25 between neighbouring
+// cell values).  FP32 caps the indicators at 2e37 (differences beyond 1e18;
+// squares of larger ones overflow, and the reciprocal of a sum above 8e37 is
+// subnormal), divides them by their sum and adds 1e-18:
+// the largest is then between 1/3 and 1, products of two are at least 1e-36,
+// and the largest weight is at least 3e-19 times tau5.  The floor only binds
+// where an indicator is 1e18 times below the sum, that is where its candidate
+// is flat to far below FP32 resolution of the others'.  One
+// reciprocal instead of three: 63 operations and 3 reciprocals a pair instead
+// of 64 and 5 (8.2 cycles each), 256^3 stages 1.59 + 1.70 -> 1.50 + 1.60 ms.
 template <typename T>
 __device__ __forceinline__ void wenoz_pair(T v0, T v1, T v2, T v3, T v4, T &rgt, T &lft)
 {
-    T e0, e1, e2, G0, G1, G2;
-    if constexpr (sizeof(T) == 8) {
-        // from the two inner differences (11 operations instead of 14)
-        const T da = v2 - v1, db = v2 - v3;
-        e1 = -(da + db);
-        G1 = T(0.5) * (db - da);
-        e0 = (v0 - v1) + da;
-        e2 = (v4 - v3) + db;
-        G0 = T(0.5) * e0 + da;
-        G2 = T(0.5) * e2 + db;
-    } else {
-        e0 = (v0 + v2) - T(2) * v1, e1 = (v1 + v3) - T(2) * v2, e2 = (v2 + v4) - T(2) * v3;
-        G0 = T(0.5) * v0 - T(2) * v1 + T(1.5) * v2;
-        G1 = T(0.5) * (v1 - v3);
-        G2 = T(1.5) * v2 - T(2) * v3 + T(0.5) * v4;
+    // e_k, 2 G_k and, below, 4 (beta_k + eps) from the two inner differences (the
+    // weights depend on ratios of the indicators only)
+    const T da = v2 - v1, db = v2 - v3;
+    const T e1 = -(da + db), e0 = (v0 - v1) + da, e2 = (v4 - v3) + db;
+    const T G1 = db - da, G0 = e0 + T(2) * da, G2 = e2 + T(2) * db;
+    const T c = T(13.0 / 3.0), eps = T(4) * Num<T>::weno_eps;
+    // FP64 adds eps first (one fused operation fewer); FP32 last: with eps
+    // first the FP32 Brio-Wu tube's error against the oracle moved from 8.8e-6
+    // to 1.09e-5 of its 1e-5 bound (other lengths moved either way)
+    auto beta = [&](T e, T G) -> T { return sizeof(T) == 8 ? c * e * e + (G * G + eps) : (c * e * e + G * G) + eps; };
+    T B0 = beta(e0, G0), B1 = beta(e1, G1), B2 = beta(e2, G2);
+    if constexpr (sizeof(T) == 4) {
+        // relative to their sum and at least 1e-18 of it, so that the products
+        // of two stay normal
+        B0 = Num<T>::min(B0, T(2e37));
+        B1 = Num<T>::min(B1, T(2e37));
+        B2 = Num<T>::min(B2, T(2e37));
+        const T s = Num<T>::rcp(B0 + B1 + B2);
+        B0 = B0 * s + T(1e-18);
+        B1 = B1 * s + T(1e-18);
+        B2 = B2 * s + T(1e-18);
     }
-    const T c = T(13.0 / 12.0);
-    const T eps = Num<T>::weno_eps;
-    // FP64 adds eps to G_k^2 first (one fused operation fewer per indicator);
-    // FP32 keeps eps last: the reordered sum moves FP32 results on the
-    // thinnest constrained-transport grids to the edge of their error bound
-    const T B0 = sizeof(T) == 8 ? c * e0 * e0 + (G0 * G0 + eps) : (c * e0 * e0 + G0 * G0) + eps;
-    const T B1 = sizeof(T) == 8 ? c * e1 * e1 + (G1 * G1 + eps) : (c * e1 * e1 + G1 * G1) + eps;
-    const T B2 = sizeof(T) == 8 ? c * e2 * e2 + (G2 * G2 + eps) : (c * e2 * e2 + G2 * G2) + eps;
     const T tau = Num<T>::abs(B0 - B2);
-    T nr, sr, nl, sl;
-    if constexpr (sizeof(T) == 8) {
-        // W_k = B0 B1 B2 + tau5 prod_{j != k} B_j
-        const T p12 = B1 * B2, p02 = B0 * B2, p01 = B0 * B1, P = B0 * p12;
-        const T w0 = tau * p12 + P, w1 = tau * p02 + P, w2 = tau * p01 + P;
-        // candidate deviations from v2 at the two faces, each scaled by its
-        // linear weight ((1, 6, 3)/10 right, (3, 6, 1)/10 left)
-        const T g0 = T(0.05) * G0, g1 = T(0.3) * G1, g2 = T(0.05) * G2;
-        const T d0r = e0 * T(0.1 / 12.0) + g0, d0l = e0 * T(0.3 / 12.0) - T(3) * g0;
-        const T d1r = e1 * T(0.05) - g1, d1l = e1 * T(0.05) + g1;
-        const T d2r = e2 * T(0.3 / 12.0) - T(3) * g2, d2l = e2 * T(0.1 / 12.0) + g2;
-        const T s1 = T(0.6) * w1;
-        nr = w0 * d0r + w1 * d1r + w2 * d2r;
-        nl = w0 * d0l + w1 * d1l + w2 * d2l;
-        sr = T(0.1) * w0 + (T(0.3) * w2 + s1);
-        sl = T(0.3) * w0 + (T(0.1) * w2 + s1);
-    } else {
-        const T h0 = e0 * T(1.0 / 12.0), h1 = e1 * T(1.0 / 12.0), h2 = e2 * T(1.0 / 12.0);
-        const T d0r = h0 + T(0.5) * G0, d0l = h0 - T(0.5) * G0;
-        const T d1r = h1 - T(0.5) * G1, d1l = h1 + T(0.5) * G1;
-        const T d2r = h2 - T(0.5) * G2, d2l = h2 + T(0.5) * G2;
-        const T m0 = Num<T>::min(tau * Num<T>::rcp(B0), T(1e18));
-        const T m1 = Num<T>::min(tau * Num<T>::rcp(B1), T(1e18));
-        const T m2 = Num<T>::min(tau * Num<T>::rcp(B2), T(1e18));
-        const T a1 = T(0.6) + T(0.6) * m1;
-        const T a0r = T(0.1) + T(0.1) * m0, a2r = T(0.3) + T(0.3) * m2;
-        const T a0l = T(0.3) + T(0.3) * m0, a2l = T(0.1) + T(0.1) * m2;
-        nr = a0r * d0r + a1 * d1r + a2r * d2r, sr = a0r + a1 + a2r;
-        nl = a0l * d0l + a1 * d1l + a2l * d2l, sl = a0l + a1 + a2l;
-    }
+    // W_k = B0 B1 B2 + tau5 prod_{j != k} B_j
+    const T p12 = B1 * B2, p02 = B0 * B2, p01 = B0 * B1, P = B0 * p12;
+    const T w0 = tau * p12 + P, w1 = tau * p02 + P, w2 = tau * p01 + P;
+    // candidate deviations from v2 at the two faces, each scaled by its
+    // linear weight ((1, 6, 3)/10 right, (3, 6, 1)/10 left)
+    const T g0 = T(0.025) * G0, g1 = T(0.15) * G1, g2 = T(0.025) * G2;
+    const T d0r = e0 * T(0.1 / 12.0) + g0, d0l = e0 * T(0.3 / 12.0) - T(3) * g0;
+    const T d1r = e1 * T(0.05) - g1, d1l = e1 * T(0.05) + g1;
+    const T d2r = e2 * T(0.3 / 12.0) - T(3) * g2, d2l = e2 * T(0.1 / 12.0) + g2;
+    const T s1 = T(0.6) * w1;
+    const T nr = w0 * d0r + w1 * d1r + w2 * d2r, nl = w0 * d0l + w1 * d1l + w2 * d2l;
+    const T sr = T(0.1) * w0 + (T(0.3) * w2 + s1), sl = T(0.3) * w0 + (T(0.1) * w2 + s1);
     if constexpr (sizeof(T) == 8) {
         const T inv = Num<T>::rcp(sr * sl);
         rgt = v2 + nr * (sl * inv);
@@ -415,15 +386,16 @@ template <typename T> __device__ __forceinline__ void side_prepare(Side<T> &s, T
     s.pt = s.p + T(0.5) * (bn * bn + s.bt2);
 }
 
-// twice the square of the fast speed: c_f^2 = (g p + |B|^2 + sqrt((g p - |B|^2)^2
-// + 4 g p |B_t|^2)) / (2 rho)
+// twice the square of the fast speed: with a^2 = g p / rho, b^2 = |B|^2 / rho,
+// 2 c_f^2 = a^2 + b^2 + sqrt((a^2 - b^2)^2 + 4 a^2 |B_t|^2 / rho)
 template <typename T>
 __device__ __forceinline__ T fast_sq2(const Side<T> &s, T bn2, const Phys<T> &ph)
 {
-    const T gp = ph.gamma * s.p, bsq = bn2 + s.bt2;
-    const T d = gp - bsq;
-    const T disc = Num<T>::max(T(4) * gp * s.bt2 + d * d, T(0));
-    return ((gp + bsq) + Num<T>::sqrt(disc)) * Num<T>::rcp(s.rho);
+    const T ir = Num<T>::rcp(s.rho);
+    const T a2 = ph.gamma * s.p * ir, b2 = (bn2 + s.bt2) * ir;
+    const T d = a2 - b2;
+    const T disc = Num<T>::max(T(4) * a2 * (s.bt2 * ir) + d * d, T(0));
+    return (a2 + b2) + Num<T>::sqrt(disc);
 }
 
 // total energy density (|B|^2/2 = p_T - p) and v.B
