@@ -156,11 +156,6 @@ __device__ __forceinline__ T ct_upwind_edge(const T (&vp)[4][4], const T (&vq)[4
     return Em;
 }
 
-// Tiling of the upwind EMF pass: TX x TY column tiles, z chunks of kz planes.
-struct CTTiles {
-    int tiles_x, tiles_y, kz, nblocks;
-};
-
 // Upwind edge EMFs on each cell's lower edges (Ex at (j-1/2, k-1/2), Ey at
 // (i-1/2, k-1/2), Ez at (i-1/2, j-1/2)), from the stage's input state.  A
 // workgroup owns a tile of TX x TY columns (one thread per column) and
@@ -174,7 +169,7 @@ struct CTTiles {
 // in-plane neighbours at plane k, and the cell's own x and y faces at planes
 // k-2 .. k+1 from a register window slid with the march.
 template <typename T, int TY>
-__global__ void __launch_bounds__(TX *TY) ct_emf_upwind_kernel(const CTArgs<T> a, const CTTiles g)
+__global__ void __launch_bounds__(TX *TY) ct_emf_upwind_kernel(const CTArgs<T> a, const Launch g)
 {
     constexpr int PX = TX + 3, PY = TY + 3, PL = PX * PY;  // LDS plane: columns -2 .. TX, rows -2 .. TY
     constexpr int NT = TX * TY;

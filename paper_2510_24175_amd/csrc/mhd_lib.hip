@@ -19,11 +19,6 @@
 
 using namespace mhd;
 
-// grid of a marching kernel: column tiles and z chunks of kz planes
-struct Launch {
-    int tiles_x, tiles_y, chunks, kz, nblocks;
-};
-
 struct mhd_ctx {
     mhd_config cfg;
     hipStream_t stream = nullptr;
@@ -103,15 +98,16 @@ constexpr int COMPUTE_UNITS = 256;
 constexpr int MIN_PART_BLOCKS = 4096;
 
 // z chunks of a marching kernel over tiles_x x tiles_y column tiles: the
-// number of chunks that minimises rounds x (planes per chunk + warm-up).  A
+// chunk length that minimises rounds x (planes per chunk + warm-up).  A
 // compute unit holds per_cu workgroups at a time; a round fills all units, and
 // a last round that leaves one workgroup (of two) per unit takes 0.6 of a
 // full one (measured, FP32 PLM).  warm is what starting a chunk costs, in
 // planes.  Chunks have at most 64 planes: longer ones measured no faster and
-// leave the last round's imbalance to chance.  Measured against every
-// power-of-two length (3D PLM, 32^3 to 320^3, both precisions) the choice is
-// within 6% of the best; lengths halved until the grid had 2048 workgroups
-// were up to 30% slower below 200^3.
+// leave the last round's imbalance to chance.  Measured against 15 fixed
+// lengths (32^3 to 320^3, both precisions) the choice is within 6% of the
+// best; lengths halved from 64 until the grid had 2048 workgroups (256 for
+// the adjoint) were up to 30% slower below 200^3 and split 70 planes into 32,
+// 32 and 6.
 Launch plan_march(long long nx, long long ny, long long nz, int ty, int per_cu, double warm)
 {
     Launch L;
@@ -138,54 +134,15 @@ Launch plan_march(long long nx, long long ny, long long nz, int ty, int per_cu, 
     return L;
 }
 
-// Forward stages: resident workgroups and warm-up per kernel.  FP32 PLM: two
-// 8-wave workgroups per unit, the warm-up (four loads, one z face, the halo)
-// fits 1.5 planes; FP64 PLM one.
+// Forward stages.  FP32 PLM: two 8-wave workgroups per unit, and the warm-up
+// (four loads, one z face, the halo) is worth 1.5 planes; FP64 PLM one; WENO-Z
+// one, with a warm-up (six loads, two reconstructions, one z face) of 2.  In
+// two dimensions and one there is one plane.
 Launch plan_stage(const mhd_ctx *ctx)
 {
     const bool f32 = ctx->cfg.dtype == MHD_F32, weno = ctx->cfg.limiter == MHD_WENOZ;
     const int ty = tile_rows_of(f32, weno, ctx->cfg.ndim);
-    if (ctx->cfg.ndim == 3 && !weno) return plan_march(ctx->n[0], ctx->n[1], ctx->n[2], ty, f32 ? 2 : 1, 1.5);
-    Launch L;
-    L.tiles_x = (int)((ctx->n[0] + TX - 1) / TX);
-    L.tiles_y = (int)((ctx->n[1] + ty - 1) / ty);
-    const long long tiles = (long long)L.tiles_x * L.tiles_y;
-    int kz = 1;
-    if (ctx->cfg.ndim == 3) {
-        // long z chunks amortise the warm-up planes; shorter chunks when
-        // the grid would otherwise leave compute units idle.  FP64 WENO-Z
-        // (one workgroup per compute unit) starts at 32 planes:
-        // measured 7% faster at 416^3 and 10% with constrained transport at
-        // 352^3 than 64; FP32 constrained transport at 16 planes, 2% faster
-        // at 352^3 (FP32 GLM: no gain)
-        kz = !f32 ? 32 : (ctx->cfg.ct ? 16 : 64);
-        while (kz > 4 && tiles * ((ctx->n[2] + kz - 1) / kz) < 2048) kz >>= 1;
-    }
-    L.kz = kz;
-    L.chunks = (int)((ctx->n[2] + kz - 1) / kz);
-    L.nblocks = (int)(tiles * L.chunks);
-    return L;
-}
-
-// Adjoint stages: one workgroup per compute unit; long z chunks, shortened
-// only while the grid has fewer than one workgroup per unit (the warm-up is
-// three planes of z work; one round of longer chunks measured 4% faster at
-// 128^3 than two rounds of half-length ones).
-Launch plan_adjoint(const mhd_ctx *ctx, int ty)
-{
-    Launch L;
-    L.tiles_x = (int)((ctx->n[0] + TX - 1) / TX);
-    L.tiles_y = (int)((ctx->n[1] + ty - 1) / ty);
-    const long long tiles = (long long)L.tiles_x * L.tiles_y;
-    int kz = 1;
-    if (ctx->cfg.ndim == 3) {
-        kz = 64;
-        while (kz > 4 && tiles * ((ctx->n[2] + kz - 1) / kz) < COMPUTE_UNITS) kz >>= 1;
-    }
-    L.kz = kz;
-    L.chunks = (int)((ctx->n[2] + kz - 1) / kz);
-    L.nblocks = (int)(tiles * L.chunks);
-    return L;
+    return plan_march(ctx->n[0], ctx->n[1], ctx->n[2], ty, f32 && !weno ? 2 : 1, weno ? 2.0 : 1.5);
 }
 
 template <typename T> Phys<T> make_phys(const mhd_ctx *ctx, double ch)
@@ -333,14 +290,9 @@ mhd_status launch_step_ct(mhd_ctx *ctx, const T *un, T *unext, T *u1, double dt,
     c.gamma_d = ctx->cfg.gamma;
     const int nb = (int)std::min<long long>((ctx->ncell + RED_THREADS - 1) / RED_THREADS, CFL_MAX_BLOCKS);
     c.nblocks = nb;
-    // upwind EMF tiling: z chunks of up to 32 planes, shortened until the
-    // pass has eight workgroups per compute unit
-    CTTiles ug;
-    ug.tiles_x = (a.nx + TX - 1) / TX;
-    ug.tiles_y = (a.ny + ct_emf_rows<T>() - 1) / ct_emf_rows<T>();
-    ug.kz = 32;
-    while (ug.kz > 4 && (long long)ug.tiles_x * ug.tiles_y * ((a.nz + ug.kz - 1) / ug.kz) < 8 * 256) ug.kz >>= 1;
-    ug.nblocks = ug.tiles_x * ug.tiles_y * ((a.nz + ug.kz - 1) / ug.kz);
+    // upwind EMF tiling: the LDS of one unit holds one FP64 workgroup or two
+    // FP32 ones; four planes are converted before a chunk's first
+    const Launch ug = plan_march(a.nx, a.ny, a.nz, ct_emf_rows<T>(), sizeof(T) == 4 ? 2 : 1, 2.0);
 
     hipEvent_t *ev = nullptr;
     if (ctx->timed_steps < ctx->timed_cap) ev = &ctx->events[4 * ctx->timed_steps++];
@@ -415,7 +367,8 @@ mhd_status launch_adj_stage(mhd_ctx *ctx, const T *U, const double *lamp, const 
                             double *out, double dt, double ch, double damp)
 {
     constexpr int TY = adj_tile_rows<T, NDIM>();
-    const Launch L = plan_adjoint(ctx, TY);
+    // one workgroup per compute unit; the warm-up is three planes of z work
+    const Launch L = plan_march(ctx->n[0], ctx->n[1], ctx->n[2], TY, 1, 1.2);
     AdjStageArgs<T> a;
     a.U = U;
     a.lamp = lamp;

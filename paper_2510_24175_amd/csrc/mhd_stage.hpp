@@ -38,6 +38,11 @@ constexpr int TX = 64;
 // 2..10: sums of the 9 conserved components
 constexpr int NPART = 11;
 
+// grid of a marching kernel: TX x TY column tiles and z chunks of kz planes
+struct Launch {
+    int tiles_x, tiles_y, chunks, kz, nblocks;
+};
+
 template <typename T> struct StageArgs {
     const T *uin;   // state the fluxes are built from (Un or U1); with
                     // constrained transport its components 9..11 are the
@@ -81,7 +86,7 @@ __device__ __forceinline__ bool cell_speeds(const T *u, double gamma, const doub
                                             double &smax, double &cmax)
 {
     const double rho = (double)u[RHO];
-    const double ir = 1.0 / rho;
+    const double ir = Num<double>::rcp(rho);
     const double m[3] = {(double)u[MX], (double)u[MY], (double)u[MZ]};
     const double b[3] = {(double)u[BX], (double)u[BY], (double)u[BZ]};
     const double bsq = b[0] * b[0] + b[1] * b[1] + b[2] * b[2];
