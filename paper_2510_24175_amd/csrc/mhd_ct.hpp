@@ -10,12 +10,12 @@
 // With E = -v x B the transverse field fluxes are F_x(By) = -Ez,
 // F_x(Bz) = Ey, F_y(Bx) = Ez, F_y(Bz) = -Ex, F_z(Bx) = -Ey, F_z(By) = Ex.
 // The stage kernel leaves them, for each cell's lower faces, in flx[6][ncell]
-// (x: By, Bz; y: Bx, Bz; z: Bx, By); emf_kernel forms the EMFs on each cell's
-// lower edges (Ex at (j-1/2, k-1/2), Ey at (i-1/2, k-1/2), Ez at
-// (i-1/2, j-1/2)); face_kernel applies dB/dt = -curl E.  Both are
-// element-wise passes (HBM-bound, no LDS) over a grid-stride range.  The
-// upwind EMF instead takes the stage's input state itself (the stage kernel
-// then stores no fluxes) in a z-marching tiled pass.
+// (x: By, Bz; y: Bx, Bz; z: Bx, By).  ct_update_kernel forms the EMFs on the
+// lower edges (Ex at (j-1/2, k-1/2), Ey at (i-1/2, k-1/2), Ez at (i-1/2,
+// j-1/2)) of each cell of its tile, applies dB/dt = -curl E and forms the cell
+// field in one z-marching pass.  The upwind EMFs come from a tiled pass of
+// their own over the stage's input state (the stage kernel then stores no
+// fluxes).
 #pragma once
 
 #include "mhd_reduce.hpp"
@@ -27,7 +27,7 @@ template <typename T> struct CTArgs {
     const T *uin;   // the stage's input state
     T *uout;        // the stage's output: faces and cell field written here
     const T *flx;   // [6][ncell] transverse field fluxes (stage kernel)
-    T *emf;         // [3][ncell] edge EMFs
+    T *emf;         // [3][ncell] edge EMFs (upwind)
     double *part;   // last stage: NPART x nblocks partials
     int *flag;      // non-physical flag
     int nx, ny, nz;
@@ -36,7 +36,6 @@ template <typename T> struct CTArgs {
     T idx[3];
     double gamma_d;
     double idx_d[3];
-    int nblocks;
 };
 
 // periodic neighbour of a cell coordinate one step away
@@ -50,25 +49,6 @@ __device__ __forceinline__ void ct_coords(long long c, int nx, int ny, int &i, i
     i = (int)(cc - row * (unsigned)nx);
     k = (int)(row / (unsigned)ny);
     j = (int)(row - (unsigned)k * (unsigned)ny);
-}
-
-template <typename T>
-__global__ void __launch_bounds__(RED_THREADS) ct_emf_kernel(const CTArgs<T> a)
-{
-    const long long nxy = (long long)a.nx * a.ny;
-    const T *FxBy = a.flx, *FxBz = a.flx + a.ncell, *FyBx = a.flx + 2 * a.ncell;
-    const T *FyBz = a.flx + 3 * a.ncell, *FzBx = a.flx + 4 * a.ncell, *FzBy = a.flx + 5 * a.ncell;
-    for (long long c = (long long)blockIdx.x * RED_THREADS + threadIdx.x; c < a.ncell;
-         c += (long long)gridDim.x * RED_THREADS) {
-        int i, j, k;
-        ct_coords(c, a.nx, a.ny, i, j, k);
-        const long long xm = c - i + ct_wrap(i - 1, a.nx);
-        const long long ym = c + (long long)(ct_wrap(j - 1, a.ny) - j) * a.nx;
-        const long long zm = c + (long long)(ct_wrap(k - 1, a.nz) - k) * nxy;
-        a.emf[c] = T(0.25) * ((FzBy[ym] + FzBy[c]) - (FyBz[zm] + FyBz[c]));
-        a.emf[a.ncell + c] = T(0.25) * ((FxBz[zm] + FxBz[c]) - (FzBx[xm] + FzBx[c]));
-        a.emf[2 * a.ncell + c] = T(0.25) * ((FyBx[xm] + FyBx[c]) - (FxBy[ym] + FxBy[c]));
-    }
 }
 
 // Velocity (3) and fast magnetosonic speed along each axis (3) of cell c
@@ -341,73 +321,159 @@ template <int KIND, typename T> __device__ __forceinline__ T rk_combine(T un, T 
     return un * T(1.0 / 3.0) + T(2.0 / 3.0) * (uin + dtr);
 }
 
-// Face update and cell field; the last stage also reduces the CFL maxima
-// (FP64 speeds of every cell) and the FP64 sums of the 9 cell components
-// into per-block partials.
-template <typename T, int KIND, bool LAST>
-__global__ void __launch_bounds__(RED_THREADS) ct_face_kernel(const CTArgs<T> a)
+// Edge EMFs (MEAN: arithmetic mean of the four face fluxes around each edge;
+// else read from emf), face update and cell field; the last stage also
+// reduces the CFL maxima (FP64 speeds of every cell) and the FP64 sums of the
+// 9 cell components into per-block partials.
+//
+// A workgroup owns a TX x TY tile of columns and marches along z.  A cell's
+// six faces take the EMFs of its lower edges and of those one cell up along
+// each axis: the EMFs of plane k+1 on the tile's (TX + 1) x (TY + 1) lower edges
+// go to one of two LDS planes, and a plane's faces are formed from both.  The
+// fluxes of plane k that the EMFs of plane k+1 need (FxBz, FyBz) and the new z
+// face shared by two planes stay in registers.  Bound by memory: 15, 18 and
+// 24 elements per cell (first, middle, last stage) of which each is read or
+// written once, plus neighbours that hit L1 or L2.  Two element-wise passes
+// with the EMFs in memory between them moved 6 elements more and took 0.75 +
+// 1.28, 1.55 and 1.91 ms at 352^3 FP64.
+template <typename T, int KIND, bool LAST, bool MEAN, int TY>
+__global__ void __launch_bounds__(TX *TY) ct_update_kernel(const CTArgs<T> a, const Launch g)
 {
-    const long long nxy = (long long)a.nx * a.ny, nc = a.ncell;
-    const T *Ex = a.emf, *Ey = a.emf + nc, *Ez = a.emf + 2 * nc;
+    constexpr int NT = TX * TY, EX = TX + 1, NE = EX * (TY + 1), NIT = (NE + NT - 1) / NT;
+    __shared__ T E[2][3][NE];
+    const int t = threadIdx.x, tx = t % TX, ty = t / TX;
+    const int lb = logical_block(blockIdx.x, g.nblocks);
+    const int tile_x = lb % g.tiles_x, rest = lb / g.tiles_x;
+    const int tile_y = rest % g.tiles_y, chunk = rest / g.tiles_y;
+    const int i0 = tile_x * TX, j0 = tile_y * TY;
+    const int k0 = chunk * g.kz, k1 = min(k0 + g.kz, a.nz);
+    const long long nc = a.ncell, nxy = (long long)a.nx * a.ny;
+
+    // this thread's lower-edge items: own, lower x and lower y neighbour
+    // offsets in a plane (periodic images; items past the grid are not used)
+    int eo[NIT], exm[NIT], eym[NIT];
+#pragma unroll
+    for (int m = 0; m < NIT; ++m) {
+        const int it = min(t + m * NT, NE - 1), ly = it / EX, lx = it - ly * EX;
+        const int gi = remap_index(i0 + lx, a.nx, 1), gj = remap_index(j0 + ly, a.ny, 1);
+        eo[m] = gj * a.nx + gi;
+        exm[m] = gj * a.nx + ct_wrap(gi - 1, a.nx);
+        eym[m] = ct_wrap(gj - 1, a.ny) * a.nx + gi;
+    }
+    T fxz[NIT], fyz[NIT];  // FxBz and FyBz of the plane below
+    auto load_below = [&](int k) {
+        const long long z = (long long)ct_wrap(k, a.nz) * nxy;
+#pragma unroll
+        for (int m = 0; m < NIT; ++m) {
+            if (t + m * NT < NE) {
+                fxz[m] = a.flx[nc + z + eo[m]];
+                fyz[m] = a.flx[3 * nc + z + eo[m]];
+            }
+        }
+    };
+    // EMFs of plane k into its LDS plane
+    auto edges = [&](int k) {
+        const long long z = (long long)ct_wrap(k, a.nz) * nxy;
+        T (*Ek)[NE] = E[k & 1];
+#pragma unroll
+        for (int m = 0; m < NIT; ++m) {
+            const int it = t + m * NT;
+            if (it < NE) {
+                const long long c = z + eo[m], xm = z + exm[m], ym = z + eym[m];
+                if constexpr (MEAN) {
+                    const T *FxBy = a.flx, *FxBz = a.flx + nc, *FyBx = a.flx + 2 * nc;
+                    const T *FyBz = a.flx + 3 * nc, *FzBx = a.flx + 4 * nc, *FzBy = a.flx + 5 * nc;
+                    const T xz = FxBz[c], yz = FyBz[c];
+                    Ek[0][it] = T(0.25) * ((FzBy[ym] + FzBy[c]) - (fyz[m] + yz));
+                    Ek[1][it] = T(0.25) * ((fxz[m] + xz) - (FzBx[xm] + FzBx[c]));
+                    Ek[2][it] = T(0.25) * ((FyBx[xm] + FyBx[c]) - (FxBy[ym] + FxBy[c]));
+                    fxz[m] = xz;
+                    fyz[m] = yz;
+                } else {
+                    Ek[0][it] = a.emf[c];
+                    Ek[1][it] = a.emf[nc + c];
+                    Ek[2][it] = a.emf[2 * nc + c];
+                }
+            }
+        }
+    };
+
+    const int i = i0 + tx, j = j0 + ty;
+    const bool active = (i < a.nx) & (j < a.ny);
+    const int ic = active ? i : 0, jc = active ? j : 0;
+    const long long col = (long long)jc * a.nx + ic;
+    const int dxp = ct_wrap(ic + 1, a.nx) - ic, dyp = (ct_wrap(jc + 1, a.ny) - jc) * a.nx;
+    const int e = ty * EX + tx;  // lower edges of the cell in an LDS plane
+    // new value of a face of component d from its old one and its rate
+    auto face = [&](int d, long long f, T r) -> T {
+        const long long x = (long long)(9 + d) * nc + f;
+        return rk_combine<KIND>(KIND == 1 ? T(0) : a.un[x], a.uin[x], a.dt * r);
+    };
+    // rate of the z face of plane k from that plane's EMFs
+    auto rate_z = [&](int k) -> T {
+        const T (*Ek)[NE] = E[k & 1];
+        return -((Ek[1][e + 1] - Ek[1][e]) * a.idx[0] - (Ek[0][e + EX] - Ek[0][e]) * a.idx[1]);
+    };
     double smax = 0.0, cmax = 0.0, sum[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) sum[q] = 0.0;
     bool ok = true;
-    for (long long c = (long long)blockIdx.x * RED_THREADS + threadIdx.x; c < nc;
-         c += (long long)gridDim.x * RED_THREADS) {
-        int i, j, k;
-        ct_coords(c, a.nx, a.ny, i, j, k);
-        const long long dxp = ct_wrap(i + 1, a.nx) - i;               // +x neighbour offset
-        const long long dyp = (long long)(ct_wrap(j + 1, a.ny) - j) * a.nx;
-        const long long dzp = (long long)(ct_wrap(k + 1, a.nz) - k) * nxy;
-        // new value of the lower face of axis d of cell e (e = c or a
-        // neighbour of c; its +1 neighbours along the other axes wrap the
-        // same way as c's, since e differs from c only along d)
-        auto face_new = [&](int d, long long e) -> T {
-            T r;
-            if (d == 0) r = -((Ez[e + dyp] - Ez[e]) * a.idx[1] - (Ey[e + dzp] - Ey[e]) * a.idx[2]);
-            else if (d == 1) r = -((Ex[e + dzp] - Ex[e]) * a.idx[2] - (Ez[e + dxp] - Ez[e]) * a.idx[0]);
-            else r = -((Ey[e + dxp] - Ey[e]) * a.idx[0] - (Ex[e + dyp] - Ex[e]) * a.idx[1]);
-            const long long f = (long long)(9 + d) * nc + e;
-            return rk_combine<KIND>(a.un[f], a.uin[f], a.dt * r);
-        };
-        T b[3];
+
+    if (MEAN) load_below(k0 - 1);
+    edges(k0);
+    __syncthreads();
+    T bz = active ? face(2, (long long)k0 * nxy + col, rate_z(k0)) : T(0);
+    for (int k = k0; k < k1; ++k) {
+        edges(k + 1);
+        __syncthreads();
+        if (active) {
+            const long long c = (long long)k * nxy + col;
+            const T (*E0)[NE] = E[k & 1], (*E1)[NE] = E[(k + 1) & 1];
+            // rates of the x face at the lower edges s, and of the y face
+            auto rate_x = [&](int s) -> T {
+                return -((E0[2][s + EX] - E0[2][s]) * a.idx[1] - (E1[1][s] - E0[1][s]) * a.idx[2]);
+            };
+            auto rate_y = [&](int s) -> T {
+                return -((E1[0][s] - E0[0][s]) * a.idx[2] - (E0[2][s + 1] - E0[2][s]) * a.idx[0]);
+            };
+            const T lo[3] = {face(0, c, rate_x(e)), face(1, c, rate_y(e)), bz};
+            bz = face(2, (long long)ct_wrap(k + 1, a.nz) * nxy + col, rate_z(k + 1));
+            const T hi[3] = {face(0, c + dxp, rate_x(e + 1)), face(1, c + dyp, rate_y(e + EX)), bz};
+            T b[3];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const long long up = d == 0 ? dxp : (d == 1 ? dyp : dzp);
-            const T lo = face_new(d, c), hi = face_new(d, c + up);
-            a.uout[(long long)(9 + d) * nc + c] = lo;
-            b[d] = T(0.5) * (lo + hi);
-            a.uout[(long long)(BX + d) * nc + c] = b[d];
+            for (int d = 0; d < 3; ++d) {
+                b[d] = T(0.5) * (lo[d] + hi[d]);
+                a.uout[(long long)(9 + d) * nc + c] = lo[d];
+                a.uout[(long long)(BX + d) * nc + c] = b[d];
+            }
+            if (LAST) {
+                T u[NQ];
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) u[q] = (q >= BX && q <= BZ) ? b[q - BX] : a.uout[(long long)q * nc + c];
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) sum[q] += (double)u[q];
+                ok &= cell_speeds<T, 3>(u, a.gamma_d, a.idx_d, smax, cmax);
+            }
         }
-        if (LAST) {
-            T u[NQ];
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) u[q] = (q >= BX && q <= BZ) ? b[q - BX] : a.uout[(long long)q * nc + c];
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) sum[q] += (double)u[q];
-            ok &= cell_speeds<T, 3>(u, a.gamma_d, a.idx_d, smax, cmax);
-        }
+        __syncthreads();  // plane k's EMFs are done with: plane k+2's go there
     }
     if (!ok) atomicOr(a.flag, 1);
     if (LAST) {
-        __shared__ double red[RED_THREADS / 64][NPART];
+        __shared__ double red[TY][NPART];
         double vals[NPART];
         vals[0] = wave_max(smax);
         vals[1] = wave_max(cmax);
 #pragma unroll
         for (int q = 0; q < NQ; ++q) vals[2 + q] = wave_sum(sum[q]);
-        const int w = threadIdx.x / 64;
-        if ((threadIdx.x & 63) == 0) {
+        if (tx == 0) {
 #pragma unroll
-            for (int e = 0; e < NPART; ++e) red[w][e] = vals[e];
+            for (int x = 0; x < NPART; ++x) red[ty][x] = vals[x];
         }
         __syncthreads();
-        if (threadIdx.x < NPART) {
-            const int e = threadIdx.x;
-            double r = red[0][e];
-            for (int x = 1; x < RED_THREADS / 64; ++x) r = e < 2 ? __builtin_fmax(r, red[x][e]) : r + red[x][e];
-            a.part[(long long)e * a.nblocks + blockIdx.x] = r;
+        if (t < NPART) {
+            double r = red[0][t];
+            for (int w = 1; w < TY; ++w) r = t < 2 ? __builtin_fmax(r, red[w][t]) : r + red[w][t];
+            a.part[(long long)t * g.nblocks + lb] = r;
         }
     }
 }

@@ -29,12 +29,12 @@ struct mhd_ctx {
     int ns = NQ;                 // state components (12 with constrained transport)
     void *u1_scratch = nullptr;  // stage-1 state when the caller passes none
     void *u2_scratch = nullptr;  // SSP-RK3 stage-2 state
-    void *ct_flx = nullptr;      // constrained transport: [6] transverse field fluxes (mean EMF)
-                                 // or cell velocities and fast speeds (upwind EMF)
-    void *ct_emf = nullptr;      // constrained transport: [3] edge EMFs
+    void *ct_flx = nullptr;      // constrained transport, mean EMF: [6] transverse field fluxes
+    void *ct_emf = nullptr;      // constrained transport, upwind EMF: [3] edge EMFs
     double *part = nullptr;      // NPART x part_cap block partials
     int part_cap = 0;
     Launch plan = {};            // grid of the forward stages
+    Launch ct_plan = {};         // grid of the constrained-transport update
     double *result = nullptr;    // device NPART doubles: reductions of the last mhd_step output
     double *cfl_result = nullptr; // device NPART doubles: the last mhd_cfl_dt reduction
     int *flag = nullptr;         // device non-physical flag
@@ -57,6 +57,8 @@ constexpr int CFL_MAX_BLOCKS = 4096;
 // rows of an upwind EMF tile (TX x 8 columns: 124 KB of LDS in FP64, one
 // workgroup of 8 waves per compute unit; 62 KB in FP32, two)
 template <typename T> constexpr int ct_emf_rows() { return 8; }
+// rows of a constrained-transport update tile (64 x 8 columns)
+constexpr int CT_UPD_ROWS = 8;
 
 mhd_status fail(mhd_ctx *ctx, mhd_status st, const char *msg)
 {
@@ -239,9 +241,10 @@ mhd_status launch_step(mhd_ctx *ctx, const T *un, T *unext, T *u1, double dt, do
 
 // Constrained transport step (3D, periodic): per stage the stage kernel
 // (fluxes with the faces' normal field, with the mean EMF the transverse
-// field fluxes to scratch, cell update of rho, m, E), the edge EMFs (mean of
-// those fluxes, or upwind from the stage's input state), and the face update
-// with the cell field; the last face update reduces the CFL maxima and sums.
+// field fluxes to scratch, cell update of rho, m, E), with the upwind EMF the
+// edge EMFs from the stage's input state, and the face update with the cell
+// field (from the EMFs or the mean of the fluxes); the last one reduces the
+// CFL maxima and sums.
 template <typename T, int SOLVER, int LIM>
 mhd_status launch_step_ct(mhd_ctx *ctx, const T *un, T *unext, T *u1, double dt, double ch, double damp)
 {
@@ -288,11 +291,10 @@ mhd_status launch_step_ct(mhd_ctx *ctx, const T *un, T *unext, T *u1, double dt,
         c.idx_d[d] = a.idx_d[d];
     }
     c.gamma_d = ctx->cfg.gamma;
-    const int nb = (int)std::min<long long>((ctx->ncell + RED_THREADS - 1) / RED_THREADS, CFL_MAX_BLOCKS);
-    c.nblocks = nb;
     // upwind EMF tiling: the LDS of one unit holds one FP64 workgroup or two
     // FP32 ones; four planes are converted before a chunk's first
     const Launch ug = plan_march(a.nx, a.ny, a.nz, ct_emf_rows<T>(), sizeof(T) == 4 ? 2 : 1, 2.0);
+    const Launch &up = ctx->ct_plan;
 
     hipEvent_t *ev = nullptr;
     if (ctx->timed_steps < ctx->timed_cap) ev = &ctx->events[4 * ctx->timed_steps++];
@@ -308,14 +310,17 @@ mhd_status launch_step_ct(mhd_ctx *ctx, const T *un, T *unext, T *u1, double dt,
         HIP_TRY(ctx, hipGetLastError());
         c.uin = uin;
         c.uout = uout;
-        if (ctx->cfg.ct == 2)
+        const dim3 grid(up.nblocks), block(TX * CT_UPD_ROWS);
+        if (ctx->cfg.ct == 2) {
             hipLaunchKernelGGL((ct_emf_upwind_kernel<T, ct_emf_rows<T>()>), dim3(ug.nblocks), dim3(TX * ct_emf_rows<T>()), 0,
                                ctx->stream, c, ug);
-        else
-            hipLaunchKernelGGL(ct_emf_kernel<T>, dim3(nb), dim3(RED_THREADS), 0, ctx->stream, c);
-        HIP_TRY(ctx, hipGetLastError());
-        hipLaunchKernelGGL((ct_face_kernel<T, KIND, last_stage(KIND)>), dim3(nb), dim3(RED_THREADS), 0,
-                           ctx->stream, c);
+            HIP_TRY(ctx, hipGetLastError());
+            hipLaunchKernelGGL((ct_update_kernel<T, KIND, last_stage(KIND), false, CT_UPD_ROWS>), grid, block, 0,
+                               ctx->stream, c, up);
+        } else {
+            hipLaunchKernelGGL((ct_update_kernel<T, KIND, last_stage(KIND), true, CT_UPD_ROWS>), grid, block, 0,
+                               ctx->stream, c, up);
+        }
         HIP_TRY(ctx, hipGetLastError());
         return MHD_OK;
     };
@@ -334,7 +339,7 @@ mhd_status launch_step_ct(mhd_ctx *ctx, const T *un, T *unext, T *u1, double dt,
     if (st != MHD_OK) return st;
     if (ev) HIP_TRY(ctx, hipEventRecord(ev[2], ctx->stream));
     hipLaunchKernelGGL(final_reduce_kernel, dim3(1), dim3(RED_THREADS), 0, ctx->stream,
-                       (const double *)ctx->part, nb, ctx->result);
+                       (const double *)ctx->part, up.nblocks, ctx->result);
     HIP_TRY(ctx, hipGetLastError());
     if (ev) HIP_TRY(ctx, hipEventRecord(ev[3], ctx->stream));
     return MHD_OK;
@@ -735,13 +740,14 @@ mhd_status mhd_init(const mhd_config *cfg, void *hip_stream, mhd_ctx **out)
     // partials capacity: the forward stage grid (the CFL kernel uses at most
     // CFL_MAX_BLOCKS); the adjoint writes no partials
     ctx->plan = plan_stage(ctx);
-    ctx->part_cap = std::max(ctx->plan.nblocks, CFL_MAX_BLOCKS);
+    if (cfg->ct) ctx->ct_plan = plan_march(ctx->n[0], ctx->n[1], ctx->n[2], CT_UPD_ROWS, 2, 1.0);
+    ctx->part_cap = std::max({ctx->plan.nblocks, ctx->ct_plan.nblocks, CFL_MAX_BLOCKS});
     ctx->ns = cfg->ct ? 12 : NQ;
     hipError_t e = hipMalloc(&ctx->u1_scratch, (size_t)ctx->ns * ctx->ncell * ctx->elem);
     if (e == hipSuccess && cfg->time_order == 3)
         e = hipMalloc(&ctx->u2_scratch, (size_t)ctx->ns * ctx->ncell * ctx->elem);
     if (e == hipSuccess && cfg->ct == 1) e = hipMalloc(&ctx->ct_flx, (size_t)6 * ctx->ncell * ctx->elem);
-    if (e == hipSuccess && cfg->ct) e = hipMalloc(&ctx->ct_emf, (size_t)3 * ctx->ncell * ctx->elem);
+    if (e == hipSuccess && cfg->ct == 2) e = hipMalloc(&ctx->ct_emf, (size_t)3 * ctx->ncell * ctx->elem);
     if (e == hipSuccess) e = hipMalloc((void **)&ctx->part, (size_t)NPART * ctx->part_cap * sizeof(double));
     if (e == hipSuccess) e = hipMalloc((void **)&ctx->result, NPART * sizeof(double));
     if (e == hipSuccess) e = hipMalloc((void **)&ctx->cfl_result, NPART * sizeof(double));

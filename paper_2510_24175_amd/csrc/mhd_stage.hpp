@@ -342,20 +342,40 @@ stage_kernel(const StageArgs<T> a)
         for (int q = 0; q < NQ; ++q) s[q] = limited_slope<LIM>(v0[q] - vm[q], vp[q] - v0[q]);
     };
 
-    // Flux through one face of the plane (offset zk) from its two states,
-    // stored in LDS.  (x, y) is the tile cell whose lower face this is.
-    // Constrained transport: its face value is the normal field and, for the
-    // tile's own faces (mine) of grid cells, the two transverse field fluxes
-    // go to flx.
-    auto flux_item = [&](auto dir, const T *VL, const T *VR, T *dst, int fstride, long long zk, int x,
+    // Constrained transport: the cell (plane offset) whose lower face item tx
+    // of chunk ch is, and that face's value, the normal field of its Riemann
+    // problem.  Loaded one chunk ahead (the first before the plane's
+    // reconstructions): a load at the face itself exposes its latency.
+    auto face_cell = [&](int ch) -> long long {
+        int x, y;
+        if (ch < NCHX) {
+            const int it = min(ch * TX + tx, NFX - 1);
+            y = it / (TX + 1);
+            x = it - y * (TX + 1);
+        } else {
+            x = tx;
+            y = ch - NCHX;
+        }
+        return (long long)remap_index(j0 + y, a.ny, a.per[1]) * a.nx + remap_index(i0 + x, a.nx, a.per[0]);
+    };
+    auto face_field = [&](int ch, long long zk) -> T {
+        return a.uin[(ch < NCHX ? 9 : 10) * a.ncell + zk + face_cell(ch)];
+    };
+    T bn_next = T(0);
+    // Flux through a face of chunk ch of the plane (offset zk) from its two
+    // states, stored in LDS.  (x, y) is the tile cell whose lower face this
+    // is.  Constrained transport: for the tile's own faces (mine) of grid
+    // cells, the two transverse field fluxes go to flx.
+    auto flux_item = [&](auto dir, const T *VL, const T *VR, T *dst, int fstride, long long zk, int ch, int x,
                          int y, bool mine) {
         constexpr int D = decltype(dir)::value;
         T F[NQ];
         if constexpr (CT) {
-            const long long fc = zk + (long long)remap_index(j0 + y, a.ny, a.per[1]) * a.nx +
-                                 remap_index(i0 + x, a.nx, a.per[0]);
-            face_flux<T, SOLVER, true>(VL, VR, D, a.ph, F, a.uin[(9 + D) * a.ncell + fc]);
+            const T bn = bn_next;
+            if (ch + NW < NCHUNK) bn_next = face_field(ch + NW, zk);
+            face_flux<T, SOLVER, true>(VL, VR, D, a.ph, F, bn);
             if (mine && (i0 + x < a.nx) & (j0 + y < a.ny) && a.flx) {
+                const long long fc = zk + face_cell(ch);
                 a.flx[(2 * D) * a.ncell + fc] = F[D == 0 ? BY : BX];
                 a.flx[(2 * D + 1) * a.ncell + fc] = F[BZ];
             }
@@ -367,7 +387,7 @@ stage_kernel(const StageArgs<T> a)
     };
     // PLM face from the LDS stencil w0..w3 (stride apart; the face lies
     // between w1 and w2): limited slopes of w1 and w2, face states, flux.
-    auto face_item = [&](auto dir, const T *base, int stride, T *dst, int fstride, long long zk, int x,
+    auto face_item = [&](auto dir, const T *base, int stride, T *dst, int fstride, long long zk, int ch, int x,
                          int y, bool mine) {
         T VL[NQ], VR[NQ];
 #pragma unroll
@@ -379,7 +399,7 @@ stage_kernel(const StageArgs<T> a)
             VL[q] = w1 + T(0.5) * s1;
             VR[q] = w2 - T(0.5) * s2;
         }
-        flux_item(dir, VL, VR, dst, fstride, zk, x, y, mine);
+        flux_item(dir, VL, VR, dst, fstride, zk, ch, x, y, mine);
     };
 
     // z window.  PLM: the conserved U(k+1), the limited slope D0 of V(k) and the
@@ -570,8 +590,10 @@ stage_kernel(const StageArgs<T> a)
         __syncthreads();
         for (int k = k0; k < k1; ++k) {
             const long long c = zoff(k) + own;
-            T un2[NQ];
+            T un2[NQ], bnz = T(0);
+            if (CT && wave < NCHUNK) bn_next = face_field(wave, zoff(k));
             if (NDIM == 3) load_cell(a.uin, a.ncell, zoff(k + 2) + own, un2);
+            if (CT) bnz = a.uin[11 * a.ncell + zoff(k + 1) + own];
             // x and y faces of the plane.  Items go out in 64-wide chunks, one
             // chunk per wave at a time; x items are padded to whole chunks so
             // every chunk is a single direction and the solver is inlined with
@@ -583,13 +605,13 @@ stage_kernel(const StageArgs<T> a)
                     const int r = it / (TX + 1), f = it - r * (TX + 1);
                     // cells f-2 .. f+1 of row r
                     face_item(std::integral_constant<int, 0>{}, &P[(r + HY) * PX + f], 1, &FXs[it],
-                              TY * (TX + 1), zoff(k), f, r, f < TX);
+                              TY * (TX + 1), zoff(k), ch, f, r, f < TX);
                 } else {
                     const int it = (ch - NCHX) * TX + tx;
                     const int r = it / TX, f = it - r * TX;
                     // rows r-2 .. r+1 of column f
                     face_item(std::integral_constant<int, 1>{}, &P[r * PX + f + H], PX, &FYs[it],
-                              (TY + 1) * TX, zoff(k), f, r, r < TY);
+                              (TY + 1) * TX, zoff(k), ch, f, r, r < TY);
                 }
             }
             __syncthreads();
@@ -609,7 +631,7 @@ stage_kernel(const StageArgs<T> a)
                     VR[q] = V1[q] - T(0.5) * D1[q];
                 }
                 if constexpr (CT)
-                    face_flux<T, SOLVER, true>(VL, VR, 2, a.ph, Fzp, a.uin[11 * a.ncell + zoff(k + 1) + own]);
+                    face_flux<T, SOLVER, true>(VL, VR, 2, a.ph, Fzp, bnz);
                 else
                     face_flux<T, SOLVER>(VL, VR, 2, a.ph, Fzp);
             }
@@ -649,6 +671,9 @@ stage_kernel(const StageArgs<T> a)
     if constexpr (WENO) {
         for (int k = k0; k < k1; ++k) {
             const long long zk = zoff(k);
+            T bnz = T(0);
+            if (CT && wave < NCHUNK) bn_next = face_field(wave, zk);
+            if (CT && owner) bnz = a.uin[11 * a.ncell + zoff(k + 1) + own];
             // the fluxes of the previous plane sit where P goes; the helpers
             // read the previous plane's results
             if ((ALIAS || HELP_RED) && k > k0) __syncthreads();
@@ -687,7 +712,7 @@ stage_kernel(const StageArgs<T> a)
                     wenoz_pair(Wz[0][q], Wz[1][q], Wz[2][q], Wz[3][q], Vn[q], ZT[q], VR[q]);
                 }
                 if constexpr (CT)
-                    face_flux<T, SOLVER, true>(VL, VR, 2, a.ph, Fzp, a.uin[11 * a.ncell + zoff(k + 1) + own]);
+                    face_flux<T, SOLVER, true>(VL, VR, 2, a.ph, Fzp, bnz);
                 else
                     face_flux<T, SOLVER>(VL, VR, 2, a.ph, Fzp);
                 // The flux is used after the x/y faces: without a use here the
@@ -765,7 +790,7 @@ stage_kernel(const StageArgs<T> a)
                         VL[q] = EX[q * QS + r * NXE + f];
                         VR[q] = EX[NQ * QS + q * QS + r * NXE + f + 1];
                     }
-                    flux_item(std::integral_constant<int, 0>{}, VL, VR, &FXs[it], TY * (TX + 1), zk, f, r, f < TX);
+                    flux_item(std::integral_constant<int, 0>{}, VL, VR, &FXs[it], TY * (TX + 1), zk, ch, f, r, f < TX);
                 } else {
                     const int it = (ch - NCHX) * TX + tx;
                     const int r = it / TX, c = it - r * TX;
@@ -775,7 +800,7 @@ stage_kernel(const StageArgs<T> a)
                         VL[q] = EY[q * QS + r * TX + c];
                         VR[q] = EY[NQ * QS + q * QS + (r + 1) * TX + c];
                     }
-                    flux_item(std::integral_constant<int, 1>{}, VL, VR, &FYs[it], (TY + 1) * TX, zk, c, r, r < TY);
+                    flux_item(std::integral_constant<int, 1>{}, VL, VR, &FYs[it], (TY + 1) * TX, zk, ch, c, r, r < TY);
                 }
             }
             __syncthreads();
