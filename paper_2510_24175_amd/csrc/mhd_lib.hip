@@ -136,14 +136,18 @@ Launch plan_march(long long nx, long long ny, long long nz, int ty, int per_cu, 
     return L;
 }
 
-// Forward stages.  FP32 PLM: two 8-wave workgroups per unit, and the warm-up
-// (four loads, one z face, the halo) is worth 1.5 planes; FP64 PLM one; WENO-Z
-// one, with a warm-up (six loads, two reconstructions, one z face) of 2.  In
-// two dimensions and one there is one plane.
+// Forward stages.  3D FP32 PLM: two 8-wave workgroups per unit, and the
+// warm-up (four loads, one z face, the halo) is worth 1.5 planes; FP64 PLM one;
+// WENO-Z one, with a warm-up (six loads, two reconstructions, one z face) of 2.
+// In two dimensions the march is over the tiles of a strip along y (4-row PLM
+// tiles: four FP32 workgroups per unit or two FP64 ones), whose start and
+// final reduction cost about a tile.
 Launch plan_stage(const mhd_ctx *ctx)
 {
     const bool f32 = ctx->cfg.dtype == MHD_F32, weno = ctx->cfg.limiter == MHD_WENOZ;
     const int ty = tile_rows_of(f32, weno, ctx->cfg.ndim);
+    if (ctx->cfg.ndim < 3)
+        return plan_march(ctx->n[0], 1, (ctx->n[1] + ty - 1) / ty, 1, weno ? 1 : (f32 ? 4 : 2), 1.0);
     return plan_march(ctx->n[0], ctx->n[1], ctx->n[2], ty, f32 && !weno ? 2 : 1, weno ? 2.0 : 1.5);
 }
 
@@ -232,7 +236,7 @@ mhd_status launch_step(mhd_ctx *ctx, const T *un, T *unext, T *u1, double dt, do
         HIP_TRY(ctx, hipGetLastError());
     }
     if (ev) HIP_TRY(ctx, hipEventRecord(ev[2], ctx->stream));
-    hipLaunchKernelGGL(final_reduce_kernel, dim3(1), dim3(RED_THREADS), 0, ctx->stream,
+    hipLaunchKernelGGL(final_reduce_kernel, dim3(NPART), dim3(FINAL_THREADS), 0, ctx->stream,
                        (const double *)ctx->part, L.nblocks, ctx->result);
     HIP_TRY(ctx, hipGetLastError());
     if (ev) HIP_TRY(ctx, hipEventRecord(ev[3], ctx->stream));
@@ -338,7 +342,7 @@ mhd_status launch_step_ct(mhd_ctx *ctx, const T *un, T *unext, T *u1, double dt,
     }
     if (st != MHD_OK) return st;
     if (ev) HIP_TRY(ctx, hipEventRecord(ev[2], ctx->stream));
-    hipLaunchKernelGGL(final_reduce_kernel, dim3(1), dim3(RED_THREADS), 0, ctx->stream,
+    hipLaunchKernelGGL(final_reduce_kernel, dim3(NPART), dim3(FINAL_THREADS), 0, ctx->stream,
                        (const double *)ctx->part, up.nblocks, ctx->result);
     HIP_TRY(ctx, hipGetLastError());
     if (ev) HIP_TRY(ctx, hipEventRecord(ev[3], ctx->stream));
@@ -507,7 +511,7 @@ mhd_status launch_cfl(mhd_ctx *ctx, const T *U)
                            ctx->ncell, ctx->cfg.gamma, i0, i1, i2, ctx->part, nb, ctx->flag);
     }
     HIP_TRY(ctx, hipGetLastError());
-    hipLaunchKernelGGL(final_reduce_kernel, dim3(1), dim3(RED_THREADS), 0, ctx->stream,
+    hipLaunchKernelGGL(final_reduce_kernel, dim3(2), dim3(FINAL_THREADS), 0, ctx->stream,
                        (const double *)ctx->part, nb, ctx->cfl_result);
     HIP_TRY(ctx, hipGetLastError());
     return MHD_OK;

@@ -9,7 +9,7 @@ namespace mhd {
 constexpr int RED_THREADS = 256;
 
 // Per-block FP64 maxima of (|v_d|+c_f,d)/dx_d and |v_d|+c_f,d over a
-// grid-stride range of cells; partials [2][nblocks] (sums left zero).
+// grid-stride range of cells; partials [2][nblocks].
 template <typename T, int NDIM>
 __global__ void __launch_bounds__(RED_THREADS)
 cfl_kernel(const T *__restrict__ U, long long ncell, double gamma, double idx0, double idx1,
@@ -38,7 +38,6 @@ cfl_kernel(const T *__restrict__ U, long long ncell, double gamma, double idx0, 
         double r = red[threadIdx.x][0];
         for (int k = 1; k < RED_THREADS / 64; ++k) r = __builtin_fmax(r, red[threadIdx.x][k]);
         part[(long long)threadIdx.x * nblocks + blockIdx.x] = r;
-        for (int e = 2 + threadIdx.x; e < NPART; e += 2) part[(long long)e * nblocks + blockIdx.x] = 0.0;
     }
 }
 
@@ -46,35 +45,29 @@ cfl_kernel(const T *__restrict__ U, long long ncell, double gamma, double idx0, 
 // caller may capture it in a HIP graph).
 __global__ void clear_flag_kernel(int *flag) { *flag = 0; }
 
-// One workgroup folds nblocks partials into out[NPART] in a fixed order:
-// each thread runs over a strided subset sequentially, then a fixed tree.
-__global__ void __launch_bounds__(RED_THREADS)
+// Folds nblocks partials of quantity blockIdx.x into out[blockIdx.x] in a
+// fixed order: each thread runs over a strided subset sequentially, then the
+// waves and their results.  Bound by the latency of its loads: a workgroup
+// per quantity and 1024 threads leave four dependent rounds for 4096
+// partials (one workgroup of 256 threads for all eleven: 8.9 us against 3-4).
+constexpr int FINAL_THREADS = 1024;
+__global__ void __launch_bounds__(FINAL_THREADS)
 final_reduce_kernel(const double *__restrict__ part, int nblocks, double *out)
 {
-    __shared__ double red[NPART][RED_THREADS];
-    const int t = threadIdx.x;
-    double acc[NPART];
-#pragma unroll
-    for (int e = 0; e < NPART; ++e) acc[e] = 0.0;
-    for (int b = t; b < nblocks; b += RED_THREADS) {
-        acc[0] = __builtin_fmax(acc[0], part[b]);
-        acc[1] = __builtin_fmax(acc[1], part[(long long)nblocks + b]);
-#pragma unroll
-        for (int e = 2; e < NPART; ++e) acc[e] += part[(long long)e * nblocks + b];
-    }
-#pragma unroll
-    for (int e = 0; e < NPART; ++e) red[e][t] = acc[e];
+    __shared__ double red[FINAL_THREADS / 64];
+    const int t = threadIdx.x, e = blockIdx.x;
+    const bool mx = e < 2;
+    const double *p = part + (long long)e * nblocks;
+    double acc = 0.0;
+    for (int b = t; b < nblocks; b += FINAL_THREADS) acc = mx ? __builtin_fmax(acc, p[b]) : acc + p[b];
+    acc = mx ? wave_max(acc) : wave_sum(acc);
+    if ((t & 63) == 0) red[t / 64] = acc;
     __syncthreads();
-    for (int s = RED_THREADS / 2; s > 0; s >>= 1) {
-        if (t < s) {
-            red[0][t] = __builtin_fmax(red[0][t], red[0][t + s]);
-            red[1][t] = __builtin_fmax(red[1][t], red[1][t + s]);
-#pragma unroll
-            for (int e = 2; e < NPART; ++e) red[e][t] += red[e][t + s];
-        }
-        __syncthreads();
+    if (t < 64) {
+        double r = t < FINAL_THREADS / 64 ? red[t] : 0.0;  // the maxima are of non-negative speeds
+        r = mx ? wave_max(r) : wave_sum(r);
+        if (t == 0) out[e] = r;
     }
-    if (t < NPART) out[t] = red[t][0];
 }
 
 // V (double primitives) -> U (state type): E in FP64, one rounding.

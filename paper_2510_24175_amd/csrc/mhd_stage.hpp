@@ -279,50 +279,61 @@ stage_kernel(const StageArgs<T> a)
     const int lb = logical_block(blockIdx.x, a.nblocks);
     const int tile_x = lb % a.tiles_x;
     const int rest = lb / a.tiles_x;
-    const int tile_y = rest % a.tiles_y;
+    // 3D: planes [k0, k1) of one column tile.  In two dimensions the march is
+    // over the tiles [k0, k1) of a strip along y (in one, a single tile).
+    const int tile_y = NDIM == 3 ? rest % a.tiles_y : 0;
     const int chunk = rest / a.tiles_y;
-    const int i0 = tile_x * TX, j0 = tile_y * TY;
+    const int i0 = tile_x * TX;
     const int k0 = chunk * a.kz;
-    const int k1 = min(k0 + a.kz, a.nz);
-    const int i = i0 + tx, j = j0 + ty;
-    const bool active = owner & (i < a.nx) & (j < a.ny);
-
+    const int k1 = min(k0 + a.kz, NDIM == 3 ? a.nz : (a.ny + TY - 1) / TY);
+    const int i = i0 + tx;
+    int j0 = 0;
+    bool active = false;
     // own column (remapped so that columns just past the grid edge hold the
     // ghost values their active neighbours need)
-    const long long own = (long long)remap_index(j, a.ny, a.per[1]) * a.nx +
-                          remap_index(i, a.nx, a.per[0]);
-    // halo cells of this thread (fixed over the march): LDS slot and offset
+    auto own_of = [&](int row0) -> long long {
+        return (long long)remap_index(row0 + ty, a.ny, a.per[1]) * a.nx + remap_index(i, a.nx, a.per[0]);
+    };
+    long long own = 0;
+    // halo cells of this thread: LDS slot and offset
     constexpr int HPT = (NH + NT - 1) / NT;  // halo cells per thread
     int h_slot[HPT];
     long long h_off[HPT];
+    // the tile whose first row is row0
+    auto set_tile = [&](int row0) {
+        j0 = row0;
+        active = owner & (i < a.nx) & (j0 + ty < a.ny);
+        own = own_of(j0);
 #pragma unroll
-    for (int m = 0; m < HPT; ++m) {
-        const int h = t + m * NT;
-        h_slot[m] = 0;
-        h_off[m] = 0;
-        if (h < NH) {
-            int lx, ly;
-            if (h < NHX) {
-                const int r = h / (2 * H), s = h % (2 * H);
-                lx = s < H ? s : TX + s;
-                ly = r + HY;
-            } else {
-                const int hy = h - NHX;
-                const int rh = hy / TX, c = hy % TX;
-                lx = c + H;
-                ly = rh < H ? rh : TY + rh;
+        for (int m = 0; m < HPT; ++m) {
+            const int h = t + m * NT;
+            h_slot[m] = 0;
+            h_off[m] = 0;
+            if (h < NH) {
+                int lx, ly;
+                if (h < NHX) {
+                    const int r = h / (2 * H), s = h % (2 * H);
+                    lx = s < H ? s : TX + s;
+                    ly = r + HY;
+                } else {
+                    const int hy = h - NHX;
+                    const int rh = hy / TX, c = hy % TX;
+                    lx = c + H;
+                    ly = rh < H ? rh : TY + rh;
+                }
+                h_slot[m] = ly * PX + lx;
+                const int gi = remap_index(i0 + lx - H, a.nx, a.per[0]);
+                const int gj = remap_index(j0 + ly - HY, a.ny, a.per[1]);
+                h_off[m] = (long long)gj * a.nx + gi;
             }
-            h_slot[m] = ly * PX + lx;
-            const int gi = remap_index(i0 + lx - H, a.nx, a.per[0]);
-            const int gj = remap_index(j0 + ly - HY, a.ny, a.per[1]);
-            h_off[m] = (long long)gj * a.nx + gi;
         }
-    }
+    };
+    set_tile((NDIM == 3 ? tile_y : k0) * TY);
     const int own_slot = (ty + HY) * PX + tx + H;
     bool ok = true;
 
     auto zoff = [&](int k) -> long long {
-        return (long long)remap_index(k, a.nz, a.per[2]) * a.nxy;
+        return NDIM == 3 ? (long long)remap_index(k, a.nz, a.per[2]) * a.nxy : 0;
     };
     auto prim_at = [&](long long c, T *v) {
         T u[NQ];
@@ -415,9 +426,10 @@ stage_kernel(const StageArgs<T> a)
     // in ZT[0..1]: registers the owners hold through the march anyway and
     // the helpers have no other use for.  Cells outside the grid count
     // nothing.
+    int j0_out = j0;  // first row of the tile whose results are in OUTS
     auto helper_fold = [&]() {
         const int row = wave - TY;
-        if ((i < a.nx) & (j0 + row < a.ny)) {
+        if ((i < a.nx) & (j0_out + row < a.ny)) {
             T u[NQ];
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
@@ -475,17 +487,10 @@ stage_kernel(const StageArgs<T> a)
             face_flux<T, SOLVER, true>(VL, VR, 2, a.ph, Fzm, a.uin[11 * a.ncell + zoff(k0) + own]);
         else
             face_flux<T, SOLVER>(VL, VR, 2, a.ph, Fzm);
-    } else if constexpr (WENO) {
-        if (owner) prim_at(own, Wz[ZC]);
-    } else {
-        T V0[NQ];
-        prim_at_keep(own, V0, me0);
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) P[q * PLANE + own_slot] = V0[q];
     }
 
     double smax = 0.0, cmax = 0.0;
-    // FP32 states: the z index of this thread's cells with the largest FP32
+    // FP32 states: the plane (tile of the strip) of this thread's cells with the largest FP32
     // estimates of the two maxima (their FP64 speeds are taken at the end)
     float best_s = -1.0f, best_c = -1.0f;
     int k_s = -1, k_c = -1;
@@ -584,20 +589,11 @@ stage_kernel(const StageArgs<T> a)
                 }
             }
         };
-        T hu[HPT][NQ];
-        load_halo(zoff(k0), hu);
-        put_halo(hu);
-        __syncthreads();
-        for (int k = k0; k < k1; ++k) {
-            const long long c = zoff(k) + own;
-            T un2[NQ], bnz = T(0);
-            if (CT && wave < NCHUNK) bn_next = face_field(wave, zoff(k));
-            if (NDIM == 3) load_cell(a.uin, a.ncell, zoff(k + 2) + own, un2);
-            if (CT) bnz = a.uin[11 * a.ncell + zoff(k + 1) + own];
-            // x and y faces of the plane.  Items go out in 64-wide chunks, one
-            // chunk per wave at a time; x items are padded to whole chunks so
-            // every chunk is a single direction and the solver is inlined with
-            // a compile-time frame.
+        // x and y faces of plane k.  Items go out in 64-wide chunks, one
+        // chunk per wave at a time; x items are padded to whole chunks so
+        // every chunk is a single direction and the solver is inlined with a
+        // compile-time frame.
+        auto plane_faces = [&](int k) {
             for (int ch = wave; ch < NCHUNK; ch += NW) {
                 if (ch < NCHX) {
                     // lanes past the last item repeat it (same values, same slot)
@@ -614,37 +610,75 @@ stage_kernel(const StageArgs<T> a)
                               (TY + 1) * TX, zoff(k), ch, f, r, r < TY);
                 }
             }
+        };
+        T hu[HPT][NQ];
+        load_halo(zoff(k0), hu);
+        if constexpr (NDIM < 3) {
+            // a strip of tiles; the next tile's cells are loaded before the
+            // faces of one and used after them
+            T uo[NQ];
+            load_cell(a.uin, a.ncell, own, uo);
+            for (int k = k0; k < k1; ++k) {
+                const long long c = own;
+                const bool mine = active;
+                T cin[NQ], cun[NQ], V0[NQ];
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) cin[q] = uo[q];
+                ok &= cons_to_prim(cin, a.ph, V0);
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) P[q * PLANE + own_slot] = V0[q];
+                put_halo(hu);
+                __syncthreads();
+                if (KIND != 1) load_cell(a.un, a.ncell, c, cun);
+                if (k + 1 < k1) {
+                    set_tile((k + 1) * TY);
+                    load_cell(a.uin, a.ncell, own, uo);
+                    load_halo(0, hu);
+                }
+                plane_faces(k);
+                __syncthreads();
+                if (mine) update(k, c, cin, cun, cun);
+            }
+        } else {
+            put_halo(hu);
             __syncthreads();
-            if (EARLY && k + 1 < k1) load_halo(zoff(k + 1), hu);
-            T V0[NQ], V1[NQ], D1[NQ], Fzp[NQ], cun[NQ];
-            if (EARLY && KIND != 1) load_cell(a.un, a.ncell, c, cun);
+            for (int k = k0; k < k1; ++k) {
+                const long long c = zoff(k) + own;
+                T un2[NQ], bnz = T(0);
+                if (CT && wave < NCHUNK) bn_next = face_field(wave, zoff(k));
+                load_cell(a.uin, a.ncell, zoff(k + 2) + own, un2);
+                if (CT) bnz = a.uin[11 * a.ncell + zoff(k + 1) + own];
+                plane_faces(k);
+                __syncthreads();
+                if (EARLY && k + 1 < k1) load_halo(zoff(k + 1), hu);
+                T V0[NQ], V1[NQ], D1[NQ], Fzp[NQ], cun[NQ];
+                if (EARLY && KIND != 1) load_cell(a.un, a.ncell, c, cun);
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) V0[q] = P[q * PLANE + own_slot];
-            if (NDIM == 3) {
-                T V2[NQ], VL[NQ], VR[NQ];
-                cons_to_prim(un1, a.ph, V1);
-                ok &= cons_to_prim(un2, a.ph, V2);
-                slope9(V0, V1, V2, D1);
+                for (int q = 0; q < NQ; ++q) V0[q] = P[q * PLANE + own_slot];
+                {
+                    T V2[NQ], VL[NQ], VR[NQ];
+                    cons_to_prim(un1, a.ph, V1);
+                    ok &= cons_to_prim(un2, a.ph, V2);
+                    slope9(V0, V1, V2, D1);
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) {
-                    VL[q] = V0[q] + T(0.5) * D0[q];
-                    VR[q] = V1[q] - T(0.5) * D1[q];
+                    for (int q = 0; q < NQ; ++q) {
+                        VL[q] = V0[q] + T(0.5) * D0[q];
+                        VR[q] = V1[q] - T(0.5) * D1[q];
+                    }
+                    if constexpr (CT)
+                        face_flux<T, SOLVER, true>(VL, VR, 2, a.ph, Fzp, bnz);
+                    else
+                        face_flux<T, SOLVER>(VL, VR, 2, a.ph, Fzp);
                 }
-                if constexpr (CT)
-                    face_flux<T, SOLVER, true>(VL, VR, 2, a.ph, Fzp, bnz);
-                else
-                    face_flux<T, SOLVER>(VL, VR, 2, a.ph, Fzp);
-            }
-            if (active) {
-                if (!EARLY && KIND != 1) load_cell(a.un, a.ncell, c, cun);
-                if (ME_LDS) {
+                if (active) {
+                    if (!EARLY && KIND != 1) load_cell(a.un, a.ncell, c, cun);
+                    if (ME_LDS) {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) me0[q] = ME[q * TY * TX + t];
+                        for (int q = 0; q < 4; ++q) me0[q] = ME[q * TY * TX + t];
+                    }
+                    const T cin[NQ] = {V0[RHO], me0[0], me0[1], me0[2], me0[3], V0[BX], V0[BY], V0[BZ], V0[PSI]};
+                    update(k, c, cin, cun, Fzp);
                 }
-                const T cin[NQ] = {V0[RHO], me0[0], me0[1], me0[2], me0[3], V0[BX], V0[BY], V0[BZ], V0[PSI]};
-                update(k, c, cin, cun, Fzp);
-            }
-            if (NDIM == 3) {
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) {
                     P[q * PLANE + own_slot] = V1[q];
@@ -671,6 +705,11 @@ stage_kernel(const StageArgs<T> a)
     if constexpr (WENO) {
         for (int k = k0; k < k1; ++k) {
             const long long zk = zoff(k);
+            if constexpr (NDIM < 3) {
+                // the next tile of the strip
+                if (k > k0) set_tile(k * TY);
+                if (owner) prim_at(own, Wz[ZC]);
+            }
             T bnz = T(0);
             if (CT && wave < NCHUNK) bn_next = face_field(wave, zk);
             if (CT && owner) bnz = a.uin[11 * a.ncell + zoff(k + 1) + own];
@@ -813,6 +852,7 @@ stage_kernel(const StageArgs<T> a)
                 if (KIND != 1) load_cell(a.un, a.ncell, c, cun);
                 update(k, c, cin, cun, Fzp);
             }
+            j0_out = j0;
             if (NDIM == 3 && owner) {
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) Fzm[q] = Fzp[q];
@@ -823,48 +863,68 @@ stage_kernel(const StageArgs<T> a)
     if constexpr (LAST && sizeof(T) == 4) {
         // FP64 speeds of the selected cells, re-read from this thread's own
         // output (it stored them above)
+        auto cell_at = [&](int k) -> long long { return NDIM == 3 ? zoff(k) + own : own_of(k * TY); };
         if (k_s >= 0) {
             T u[NQ];
-            load_cell(a.uout, a.ncell, zoff(k_s) + own, u);
+            load_cell(a.uout, a.ncell, cell_at(k_s), u);
             ok &= cell_speeds<T, NDIM>(u, a.gamma_d, a.idx_d, smax, cmax);
         }
         if (k_c >= 0 && k_c != k_s) {
             T u[NQ];
-            load_cell(a.uout, a.ncell, zoff(k_c) + own, u);
+            load_cell(a.uout, a.ncell, cell_at(k_c), u);
             ok &= cell_speeds<T, NDIM>(u, a.gamma_d, a.idx_d, smax, cmax);
         }
     }
     if (LAST) {
-        // block reduction of the partials in a fixed order
+        // block reduction of the partials in a fixed order: every column's
+        // values to LDS, then wave w takes the quantities w, w + NW, ..., folds
+        // the rows per lane and the lanes by a wave reduction (two or three of
+        // the eleven a wave; all eleven in every wave made the last stage of a
+        // 1024^2 grid, with one tile per workgroup, 62 us against 34 for the
+        // first)
+        constexpr int COLS = TX * TY;
+        static_assert(NPART * COLS * 8 <= SZL * (int)sizeof(T) || NDIM == 1, "LDS for the partials");
         __syncthreads();
-        double *red = reinterpret_cast<double *>(P);  // LDS reuse, TY * NPART doubles
+        double *red = reinterpret_cast<double *>(P);  // LDS reuse
         double vals[NPART];
         if constexpr (HELP_RED) {
             if (!owner) helper_fold();  // the chunk's last plane
-            vals[0] = wave_max(ZT[0]);
-            vals[1] = wave_max(ZT[1]);
+            vals[0] = ZT[0];
+            vals[1] = ZT[1];
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) vals[2 + q] = wave_sum(Fzm[q]);
+            for (int q = 0; q < NQ; ++q) vals[2 + q] = Fzm[q];
         } else {
-            vals[0] = wave_max(smax);
-            vals[1] = wave_max(cmax);
+            vals[0] = smax;
+            vals[1] = cmax;
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) vals[2 + q] = wave_sum(sum[q]);
+            for (int q = 0; q < NQ; ++q) vals[2 + q] = sum[q];
         }
-        // the row's reducing wave: its helper, or its owner
-        if (tx == 0 && (HELP_RED ? !owner : owner)) {
-            const int row = HELP_RED ? wave - TY : ty;
+        if constexpr (NDIM == 1) {
+            // a single row: its reducing wave takes all
+            if (HELP_RED ? !owner : owner) {
 #pragma unroll
-            for (int e = 0; e < NPART; ++e) red[row * NPART + e] = vals[e];
-        }
-        __syncthreads();
-        if (t < NPART) {
-            double r = red[t];
-            for (int w = 1; w < TY; ++w) {
-                const double x = red[w * NPART + t];
-                r = t < 2 ? __builtin_fmax(r, x) : r + x;
+                for (int e = 0; e < NPART; ++e) {
+                    const double r = e < 2 ? wave_max(vals[e]) : wave_sum(vals[e]);
+                    if (tx == 0) a.part[(long long)e * a.nblocks + lb] = r;
+                }
             }
-            a.part[(long long)t * a.nblocks + lb] = r;
+        } else {
+            // the row's reducing wave: its helper, or its owner
+            if (HELP_RED ? !owner : owner) {
+                const int row = HELP_RED ? wave - TY : ty;
+#pragma unroll
+                for (int e = 0; e < NPART; ++e) red[e * COLS + row * TX + tx] = vals[e];
+            }
+            __syncthreads();
+            for (int e = wave; e < NPART; e += NW) {
+                double r = red[e * COLS + tx];
+                for (int w = 1; w < TY; ++w) {
+                    const double x = red[e * COLS + w * TX + tx];
+                    r = e < 2 ? __builtin_fmax(r, x) : r + x;
+                }
+                r = e < 2 ? wave_max(r) : wave_sum(r);
+                if (tx == 0) a.part[(long long)e * a.nblocks + lb] = r;
+            }
         }
     }
     if (!ok) atomicOr(a.flag, 1);
