@@ -948,7 +948,7 @@ __global__ void __launch_bounds__(TX *TY) adj_stage_kernel(const AdjStageArgs<T>
             }
         }
     }
-    if (!ok) atomicOr(a.flag, 1);
+    if (!ok) *a.flag = 1;
 }
 
 } // namespace mhd

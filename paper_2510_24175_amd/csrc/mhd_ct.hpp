@@ -457,7 +457,7 @@ __global__ void __launch_bounds__(TX *TY) ct_update_kernel(const CTArgs<T> a, co
         }
         __syncthreads();  // plane k's EMFs are done with: plane k+2's go there
     }
-    if (!ok) atomicOr(a.flag, 1);
+    if (!ok) *a.flag = 1;
     if (LAST) {
         __shared__ double red[TY][NPART];
         double vals[NPART];

@@ -35,10 +35,14 @@ struct mhd_ctx {
     int part_cap = 0;
     Launch plan = {};            // grid of the forward stages
     Launch ct_plan = {};         // grid of the constrained-transport update
-    double *result = nullptr;    // device NPART doubles: reductions of the last mhd_step output
-    double *cfl_result = nullptr; // device NPART doubles: the last mhd_cfl_dt reduction
-    int *flag = nullptr;         // device non-physical flag
-    double *host_res = nullptr;  // pinned NPART doubles + flag word
+    // Results and the non-physical flag are written by the kernels straight
+    // into pinned host memory (two copies of 88 and 4 bytes per read-back took
+    // 9 us of a small grid's step): the reductions of the last mhd_step output,
+    // those of the last mhd_cfl_dt, and the flag (a plain store of 1).
+    double *host_res = nullptr;  // pinned: RES_WORDS doubles
+    double *result = nullptr;    // device address of the step's NPART words (mhd_step_noalloc: device memory)
+    double *cfl_result = nullptr; // device address of the CFL's NPART words
+    int *flag = nullptr;         // device address of the flag (mhd_step_noalloc: device memory)
     double *lam1 = nullptr;      // adjoint: FP64 stage cotangent
     bool have_step = false;
     double cell_volume = 1.0;
@@ -54,6 +58,8 @@ struct mhd_ctx {
 namespace {
 
 constexpr int CFL_MAX_BLOCKS = 4096;
+// pinned result words: step results, CFL results, flag word
+constexpr int RES_CFL = NPART, RES_FLAG = 2 * NPART, RES_WORDS = 2 * NPART + 1;
 // rows of an upwind EMF tile (TX x 8 columns: 124 KB of LDS in FP64, one
 // workgroup of 8 waves per compute unit; 62 KB in FP32, two)
 template <typename T> constexpr int ct_emf_rows() { return 8; }
@@ -517,20 +523,15 @@ mhd_status launch_cfl(mhd_ctx *ctx, const T *U)
     return MHD_OK;
 }
 
-// Copy the result words of one reduction (the step's or the standalone
-// CFL's) back, wait, and report (and clear) the flag.
-mhd_status sync_results(mhd_ctx *ctx, const double *result)
+// Wait for the stream, after which host_res holds the results of the last
+// final reductions, and report (and clear) the flag.
+mhd_status sync_results(mhd_ctx *ctx)
 {
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->host_res, result, NPART * sizeof(double),
-                                hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->host_res + NPART, ctx->flag, sizeof(int), hipMemcpyDeviceToHost,
-                                ctx->stream));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     int flag;
-    std::memcpy(&flag, ctx->host_res + NPART, sizeof(int));
+    std::memcpy(&flag, ctx->host_res + RES_FLAG, sizeof(int));
     if (flag) {
-        HIP_TRY(ctx, hipMemsetAsync(ctx->flag, 0, sizeof(int), ctx->stream));
-        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+        std::memset(ctx->host_res + RES_FLAG, 0, sizeof(double));
         return fail(ctx, MHD_ERR_NONPHYSICAL, "non-physical state (rho <= 0, p <= 0 or non-finite)");
     }
     return MHD_OK;
@@ -604,9 +605,9 @@ void destroy_events(mhd_ctx *ctx)
 constexpr int NOALLOC_MAX_BLOCKS = 16384;
 constexpr size_t NOALLOC_PART_BYTES = (size_t)NPART * NOALLOC_MAX_BLOCKS * sizeof(double);
 constexpr size_t NOALLOC_RESULT_OFF = NOALLOC_PART_BYTES;
-constexpr size_t NOALLOC_FLAG_OFF = NOALLOC_RESULT_OFF + 256;
-constexpr size_t NOALLOC_BYTES = NOALLOC_FLAG_OFF + 256;
-static_assert(NPART * sizeof(double) <= 256, "result words fit their slot");
+constexpr size_t NOALLOC_FLAG_OFF = NOALLOC_RESULT_OFF + NPART * sizeof(double);  // read back with the results
+constexpr size_t NOALLOC_BYTES = NOALLOC_RESULT_OFF + 256;
+static_assert((NPART + 1) * sizeof(double) <= 256, "result and flag words fit their slot");
 __device__ __align__(256) unsigned char scratch[NOALLOC_BYTES];
 
 constexpr int NOALLOC_MAX_DEVICES = 64;
@@ -643,9 +644,6 @@ void free_ctx(mhd_ctx *ctx)
     if (ctx->ct_flx) (void)hipFree(ctx->ct_flx);
     if (ctx->ct_emf) (void)hipFree(ctx->ct_emf);
     if (ctx->part) (void)hipFree(ctx->part);
-    if (ctx->result) (void)hipFree(ctx->result);
-    if (ctx->cfl_result) (void)hipFree(ctx->cfl_result);
-    if (ctx->flag) (void)hipFree(ctx->flag);
     if (ctx->host_res) (void)hipHostFree(ctx->host_res);
     if (ctx->lam1) (void)hipFree(ctx->lam1);
     delete ctx;
@@ -753,13 +751,15 @@ mhd_status mhd_init(const mhd_config *cfg, void *hip_stream, mhd_ctx **out)
     if (e == hipSuccess && cfg->ct == 1) e = hipMalloc(&ctx->ct_flx, (size_t)6 * ctx->ncell * ctx->elem);
     if (e == hipSuccess && cfg->ct == 2) e = hipMalloc(&ctx->ct_emf, (size_t)3 * ctx->ncell * ctx->elem);
     if (e == hipSuccess) e = hipMalloc((void **)&ctx->part, (size_t)NPART * ctx->part_cap * sizeof(double));
-    if (e == hipSuccess) e = hipMalloc((void **)&ctx->result, NPART * sizeof(double));
-    if (e == hipSuccess) e = hipMalloc((void **)&ctx->cfl_result, NPART * sizeof(double));
-    if (e == hipSuccess) e = hipMalloc((void **)&ctx->flag, sizeof(int));
-    if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->host_res, (NPART + 1) * sizeof(double));
+    if (e == hipSuccess) e = hipHostMalloc((void **)&ctx->host_res, RES_WORDS * sizeof(double));
+    if (e == hipSuccess) {
+        std::memset(ctx->host_res, 0, RES_WORDS * sizeof(double));
+        e = hipHostGetDevicePointer((void **)&ctx->result, ctx->host_res, 0);
+        ctx->cfl_result = ctx->result + RES_CFL;
+        ctx->flag = (int *)(ctx->result + RES_FLAG);
+    }
     if (e == hipSuccess && (cfg->flags & MHD_FLAG_ADJOINT))
         e = hipMalloc((void **)&ctx->lam1, (size_t)NQ * ctx->ncell * sizeof(double));
-    if (e == hipSuccess) e = hipMemsetAsync(ctx->flag, 0, sizeof(int), ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) {
         free_ctx(ctx);
@@ -826,10 +826,10 @@ mhd_status mhd_cfl_dt(mhd_ctx *ctx, const void *U, double out[2])
     mhd_status st = ctx->cfg.dtype == MHD_F32 ? launch_cfl<float>(ctx, (const float *)U)
                                                : launch_cfl<double>(ctx, (const double *)U);
     if (st != MHD_OK) return st;
-    st = sync_results(ctx, ctx->cfl_result);
+    st = sync_results(ctx);
     if (st != MHD_OK) return st;
-    out[0] = ctx->cfg.cfl / ctx->host_res[0];
-    out[1] = ctx->host_res[1];
+    out[0] = ctx->cfg.cfl / ctx->host_res[RES_CFL];
+    out[1] = ctx->host_res[RES_CFL + 1];
     return MHD_OK;
 }
 
@@ -857,7 +857,7 @@ mhd_status mhd_step_info(mhd_ctx *ctx, double out[11])
     if (!ctx) return MHD_ERR_ARG;
     if (!out) return fail(ctx, MHD_ERR_ARG, "null buffer");
     if (!ctx->have_step) return fail(ctx, MHD_ERR_ARG, "no step has run on this context");
-    mhd_status st = sync_results(ctx, ctx->result);
+    mhd_status st = sync_results(ctx);
     if (st != MHD_OK) return st;
     out[0] = ctx->cfg.cfl / ctx->host_res[0];
     out[1] = ctx->host_res[1];
@@ -870,7 +870,7 @@ mhd_status mhd_get_sums(mhd_ctx *ctx, double out[9])
     if (!ctx) return MHD_ERR_ARG;
     if (!out) return fail(ctx, MHD_ERR_ARG, "null buffer");
     if (!ctx->have_step) return fail(ctx, MHD_ERR_ARG, "no step has run on this context");
-    mhd_status st = sync_results(ctx, ctx->result);
+    mhd_status st = sync_results(ctx);
     if (st != MHD_OK) return st;
     for (int q = 0; q < NQ; ++q) out[q] = ctx->host_res[2 + q] * ctx->cell_volume;
     return MHD_OK;
@@ -928,12 +928,12 @@ mhd_status mhd_step_noalloc(const mhd_config *cfg, void *hip_stream, const void 
         return launch_step_nd<typename S::T, S::SOLVER, S::LIM>(&c, Un, U_next, U1_out, dt, c_h, damp);
     });
     if (st != MHD_OK || !info) return st;
-    double res[NPART];
-    int flag = 0;
+    double res[NPART + 1];
     if (hipMemcpyAsync(res, c.result, sizeof res, hipMemcpyDeviceToHost, c.stream) != hipSuccess ||
-        hipMemcpyAsync(&flag, c.flag, sizeof flag, hipMemcpyDeviceToHost, c.stream) != hipSuccess ||
         hipStreamSynchronize(c.stream) != hipSuccess)
         return MHD_ERR_HIP;
+    int flag;
+    std::memcpy(&flag, res + NPART, sizeof flag);
     if (flag) return MHD_ERR_NONPHYSICAL;
     info[0] = cfg->cfl / res[0];
     info[1] = res[1];

@@ -24,7 +24,7 @@ cfl_kernel(const T *__restrict__ U, long long ncell, double gamma, double idx0, 
         load_cell(U, ncell, c, u);
         ok &= cell_speeds<T, NDIM>(u, gamma, idx, smax, cmax);
     }
-    if (!ok) atomicOr(flag, 1);
+    if (!ok) *flag = 1;
     __shared__ double red[2][RED_THREADS / 64];
     smax = wave_max(smax);
     cmax = wave_max(cmax);
@@ -49,7 +49,8 @@ __global__ void clear_flag_kernel(int *flag) { *flag = 0; }
 // fixed order: each thread runs over a strided subset sequentially, then the
 // waves and their results.  Bound by the latency of its loads: a workgroup
 // per quantity and 1024 threads leave four dependent rounds for 4096
-// partials (one workgroup of 256 threads for all eleven: 8.9 us against 3-4).
+// partials (one workgroup of 256 threads for all eleven: 8.9 us against 3-4). out may be
+// host memory.
 constexpr int FINAL_THREADS = 1024;
 __global__ void __launch_bounds__(FINAL_THREADS)
 final_reduce_kernel(const double *__restrict__ part, int nblocks, double *out)

@@ -927,7 +927,7 @@ stage_kernel(const StageArgs<T> a)
             }
         }
     }
-    if (!ok) atomicOr(a.flag, 1);
+    if (!ok) *a.flag = 1;
 }
 
 } // namespace mhd
