@@ -712,18 +712,28 @@ __global__ void __launch_bounds__(TX *TY) adj_stage_kernel(const AdjStageArgs<T>
         load_cell(a.U, a.ncell, c, u);
         ok &= cons_to_prim(u, a.ph, v);
     };
-    // flux cotangent of a face between cells ca and cb (-1: outside, zero)
+    // flux cotangent of a face between cells ca and cb (-1: outside, zero).
+    // FP32 reads cell 0 for a cell outside and masks it: 18 branches around
+    // the loads cost more than the loads (128^3: 700 us per step, 680 without
+    // them and with the z face before the barrier).  FP64, one wave per SIMD
+    // and no free register, keeps the branches (150 x 110 x 70: 1181 us, 1278
+    // with masks).
     auto face_g = [&](long long ca, long long cb, double idx, T *gb) {
+        const double *v = PASS == 2 ? a.lamp : a.lam1;
+        const unsigned ma = Bits<float>::opaque(ca >= 0 ? -1 : 0), mb = Bits<float>::opaque(cb >= 0 ? -1 : 0);
+        const long long pa = ca >= 0 ? ca : 0, pb = cb >= 0 ? cb : 0;
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
+            const double sc = PASS == 2 && q == PSI ? a.damp : 1.0;
             double va = 0.0, vb = 0.0;
-            if (PASS == 2) {
-                const double sc = q == PSI ? a.damp : 1.0;
-                if (ca >= 0) va = a.lamp[q * a.ncell + ca] * sc;
-                if (cb >= 0) vb = a.lamp[q * a.ncell + cb] * sc;
+            if (sizeof(T) == 4) {
+                va = Bits<double>::keep(ma, v[q * a.ncell + pa]) * sc;
+                vb = Bits<double>::keep(mb, v[q * a.ncell + pb]) * sc;
+                // the rounded products, not a fused difference of them
+                if (PASS == 2 && q == PSI) asm("" : "+v"(va), "+v"(vb));
             } else {
-                if (ca >= 0) va = a.lam1[q * a.ncell + ca];
-                if (cb >= 0) vb = a.lam1[q * a.ncell + cb];
+                if (ca >= 0) va = v[q * a.ncell + ca] * sc;
+                if (cb >= 0) vb = v[q * a.ncell + cb] * sc;
             }
             gb[q] = (T)((vb - va) * idx);
         }
@@ -819,7 +829,6 @@ __global__ void __launch_bounds__(TX *TY) adj_stage_kernel(const AdjStageArgs<T>
                     }
                 }
             }
-            __syncthreads();
         }
         // (b) z-face kk+2 and the z cell item of kk+1 (planes kk .. kk+3
         // re-read, they are cache resident); R starts as Wb_z of plane kk
@@ -860,6 +869,7 @@ __global__ void __launch_bounds__(TX *TY) adj_stage_kernel(const AdjStageArgs<T>
             for (int q = 0; q < NQ; ++q) R[q] = T(0);
         }
         if (!out) continue;
+        __syncthreads();
         // (d) cell items: own cells (x and y), then the halo cells
         {
             const int fo = ty * FXW + tx + 1;  // slot of face i (own cell's lower x face)
