@@ -5,8 +5,8 @@ and arithmetic (FP64 CFL reduction and conservation sums), PLM minmod +
 HLLD + GLM, SSP-RK2, CFL 0.3; synthetic seeded initial fields.
 
 A timed step is one pass of the whole hot path: the CFL maxima of the
-previous step's output are read back (one 16-byte device-to-host copy and
-stream sync), the GLM decay factor is formed, and mhd_step runs both stage
+previous step's output are read back (the kernels leave them in pinned host
+memory; one stream sync), the GLM decay factor is formed, and mhd_step runs both stage
 kernels with the fused ghost fill, reconstruction, Riemann fluxes, flux
 divergence, psi damping, CFL and FP64-sum reductions.  Inputs are resident
 in HBM before timing starts.
@@ -14,7 +14,7 @@ in HBM before timing starts.
 Prints one JSON line with the throughput (Mcell-updates/s), the HBM
 roofline of the dominant kernel (stage 2: algorithmic bytes per launch over
 its average duration from HIP events recorded on the library's stream,
-against 8 TB/s), beside it the VALU issue roof that binds that kernel, FP64
+against 8 TB/s), beside it the VALU issue rate that binds that kernel, FP64
 figures on the same workload, the paper's benchmark scheme
 (WENO-Z + HLLD + GLM + SSP-RK3) on its two problems (3D Orszag-Tang, 3D
 circularly polarised Alfven wave) at the per-GPU share 416^3, the
@@ -33,7 +33,11 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, GB/s
-VALU_PEAK_TLANE = 1024 * 16 * 2.4e9 / 1e12  # 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz
+# 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz: every wave64 instruction at 4 cycles.  A
+# scale rather than a bound: one kind at a time, plain FP32 operations measure 2.3-2.7
+# cycles, comparisons, selects and FP64 ones 4.3-5.3, FP32 reciprocals and roots 8.2,
+# FP64 ones 16.3.
+VALU_PEAK_TLANE = 1024 * 16 * 2.4e9 / 1e12
 METRIC = "Mcell-updates/s + % HBM roofline (FP32 vs FP64), adjoint/forward time ratio"
 
 
@@ -153,19 +157,19 @@ def run_gpu(n, dtype, steps, warmup, workload="turbulence", limiter="minmod", ti
     # per SSP-RK3 step.  Constrained transport, per stage: the stage kernel
     # reads the input's 9 components and 3 faces (and Un's 9 after the first
     # stage) and writes 6 components and 6 transverse fluxes (24 s | 33 s);
-    # the EMF pass reads 6 fluxes and writes 3 EMFs (9 s); the face pass
-    # reads 3 EMFs and the input's 3 faces (and Un's 3 after the first
-    # stage), writes 3 faces and 3 cell-field components, and in the last
-    # stage reads 6 components for the reductions (12 s | 15 s | 21 s):
-    # 45 s, 57 s and 63 s B/cell for the first, a middle and the last stage.
-    # With the upwind EMF the stage kernel writes no fluxes (18 s | 27 s) and
-    # the EMF pass reads the input's 8 cell and 3 face components and writes
-    # 3 EMFs (14 s): 44 s, 56 s and 62 s.
+    # the EMF and face pass reads the 6 fluxes and the input's 3 faces (and
+    # Un's 3 after the first stage), writes 3 faces and 3 cell-field
+    # components, and in the last stage reads 6 components for the reductions
+    # (15 s | 18 s | 24 s): 39 s, 51 s and 57 s B/cell for the first, a middle
+    # and the last stage.  With the upwind EMF the stage kernel writes no
+    # fluxes (18 s | 27 s), an EMF pass reads the input's 8 cell and 3 face
+    # components and writes 3 EMFs (14 s), and the face pass reads these in
+    # place of the fluxes (12 s | 15 s | 21 s): 44 s, 56 s and 62 s.
     if setup.get("ct", False):
         if setup.get("ct_emf") == "upwind":
             stages = [44] + [56] * (time_order - 2) + [62]
         else:
-            stages = [45] + [57] * (time_order - 2) + [63]
+            stages = [39] + [51] * (time_order - 2) + [57]
         res["alg_bytes_step"] = sum(stages) * s * ncell
     else:
         res["alg_bytes_step"] = (18 + 27 * (time_order - 1)) * s * ncell
@@ -416,7 +420,7 @@ def main():
         # what binds the kernel instead: VALU issue.  Its VALU lane
         # instructions per launch (SQ_INSTS_VALU x 64, counted on these
         # sources) over the launch duration, against 1024 SIMDs x 16 lanes at
-        # 2.4 GHz (a wave64 instruction occupies a SIMD for 4 cycles)
+        # 2.4 GHz (4 cycles per wave64 instruction)
         lane_insts = cnt["valu_wave_insts"] * 64
         alu = lane_insts / (r32["stage2_ms"] * 1e-3) / 1e12
         out["alu_roofline"] = {

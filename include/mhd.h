@@ -53,9 +53,9 @@
  *
  * Ownership: the caller owns every state, adjoint and primitive buffer.
  * The library owns the context and its scratch (stage-1 buffer when the
- * caller passes none, the SSP-RK3 stage-2 buffer, the constrained-transport
- * EMF buffer and, with the mean EMF, face-flux buffer, reduction partials,
- * result and error words), all
+ * caller passes none, the SSP-RK3 stage-2 buffer, with constrained transport
+ * the face-flux buffer of the mean EMF or the EMF buffer of the upwind one,
+ * reduction partials, result and error words in pinned host memory), all
  * allocated by mhd_init and freed by mhd_destroy; mhd_step,
  * mhd_step_adjoint and mhd_cfl_dt allocate nothing.
  *
@@ -67,7 +67,7 @@
  * Errors: every call returns an mhd_status.  Arguments are validated before
  * any device work is enqueued; on MHD_ERR_ARG nothing was enqueued.  HIP
  * failures give MHD_ERR_HIP with the text in mhd_last_error.  Kernels raise
- * a device flag on any cell with rho <= 0, p <= 0 or a non-finite value;
+ * a flag on any cell with rho <= 0, p <= 0 or a non-finite value;
  * the next syncing call returns MHD_ERR_NONPHYSICAL and clears the flag.
  */
 #ifndef MHD_H

@@ -79,7 +79,7 @@ __device__ __forceinline__ void flux_rev(const RState<T> &s, const T *fb, const 
     b.rho += cb[0] + s.v1 * cb[2] + s.v2 * cb[3] + mub * s.u;
 }
 
-// fast speed of a prepared state (same arithmetic as fast_speed), with the
+// fast speed of a prepared state, with the
 // root of the discriminant that its reverse reuses
 template <typename T>
 __device__ __forceinline__ T fast_fwd(const RState<T> &s, const Phys<T> &ph, T &sd)
@@ -251,9 +251,10 @@ __device__ __forceinline__ RState<T> pick_state(bool c, const RState<T> &a, cons
     o.pt = c ? a.pt : b.pt; o.vb = c ? a.vb : b.vb;
     return o;
 }
-// HLLD VJP on prepared states (Miyoshi & Kusano 2005, same arithmetic and
-// decisions as hlld_flux): the forward is recomputed, then reversed
-// statement by statement.  The side the flux is taken from (left of the
+// HLLD VJP on prepared states (Miyoshi & Kusano 2005): the flux is recomputed
+// as the sum over the fan (hlld_flux, the same function with the same choice
+// of states, multiplies the picked state out instead), then reversed statement
+// by statement.  The side the flux is taken from (left of the
 // contact when S_M >= 0) alone carries energies; its cotangents are added to
 // the left or right accumulators with 0/1 weights.
 template <typename T>
@@ -264,7 +265,7 @@ __device__ __forceinline__ void hlld_vjp(const RState<T> &L, const RState<T> &R,
     // ---- forward ----
     T sdL, sdR;
     const T cL = fast_fwd(L, ph, sdL), cR = fast_fwd(R, ph, sdR);
-    // outer speeds as hlld_flux; ties pick the left state
+    // outer speeds; ties pick the left state
     const bool uminl = L.u <= R.u, umaxl = L.u >= R.u, cmaxl = cL >= cR;
     const T cm = cmaxl ? cL : cR;
     const T sL = (uminl ? L.u : R.u) - cm, sR = (umaxl ? L.u : R.u) + cm;

@@ -7,8 +7,8 @@
 // A face normal to axis d is solved in the cyclic frame (n, t1, t2) =
 // (d, d+1, d+2) mod 3.  Everything is templated on the arithmetic type T
 // (float or double); reciprocals and square roots go through Num<T>, which
-// uses the hardware approximations in FP32, and in FP64 IEEE square roots and
-// Newton-refined reciprocals.
+// uses the hardware approximations in FP32, and in FP64 refines the hardware
+// estimates.
 #pragma once
 
 #include <hip/hip_runtime.h>
