@@ -701,8 +701,26 @@ stage_kernel(const StageArgs<T> a)
         }
     }
 
-    // WENO-Z
+    // WENO-Z.  In 3D the halo cells of plane k+1 are loaded before the face
+    // fluxes of plane k and converted at its start: a load issued there waits
+    // for its own latency and for the update's stores before it.  256^3 stages
+    // FP64 2.54, 2.66 and 2.79 -> 2.40, 2.57 and 2.68 ms; loaded before the
+    // reconstructions 2.45, 2.60 and 2.65, before the z faces no gain.  FP32
+    // also loads the input state of the combine there, 1.50, 1.53 and 1.61 ->
+    // 1.44, 1.50 and 1.55 ms (FP64 spills with it, and either type with Un or
+    // the own cells of plane k+4 as well).  Not with constrained transport:
+    // its FP64 stages spill 22 registers then (352^3 step 28.5 -> 33.9 ms), its
+    // FP32 ones gain nothing (176^3 2.40 -> 2.42 ms).
     if constexpr (WENO) {
+        constexpr bool AHEAD = NDIM == 3 && !CT;
+        constexpr bool EARLY_IN = AHEAD && sizeof(T) == 4;
+        T hu[HPT][NQ];
+        auto load_halo = [&](int k) {
+#pragma unroll
+            for (int m = 0; m < HPT; ++m)
+                if (t + m * NT < NH) load_cell(a.uin, a.ncell, zoff(k) + h_off[m], hu[m]);
+        };
+        if (AHEAD) load_halo(k0);
         for (int k = k0; k < k1; ++k) {
             const long long zk = zoff(k);
             if constexpr (NDIM < 3) {
@@ -725,7 +743,10 @@ stage_kernel(const StageArgs<T> a)
             for (int m = 0; m < HPT; ++m) {
                 if (t + m * NT < NH) {
                     T hv[NQ];
-                    prim_at(zk + h_off[m], hv);
+                    if (AHEAD)
+                        ok &= cons_to_prim(hu[m], a.ph, hv);
+                    else
+                        prim_at(zk + h_off[m], hv);
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) P[q * PLANE + h_slot[m]] = hv[q];
                 }
@@ -815,6 +836,9 @@ stage_kernel(const StageArgs<T> a)
                 }
             }
             __syncthreads();
+            T cin[NQ];
+            if (EARLY_IN) load_cell(a.uin, a.ncell, zk + own, cin);
+            if (AHEAD && k + 1 < k1) load_halo(k + 1);
             // (c1) face fluxes from the edge values: x face f of row r between
             // cells f-1 and f, y face r of column c between rows r-1 and r;
             // (the fluxes overwrite P when the LDS is aliased)
@@ -843,12 +867,11 @@ stage_kernel(const StageArgs<T> a)
                 }
             }
             __syncthreads();
-            // (d) divergence and stage combine (the combine's inputs loaded here:
-            // earlier loads spill in FP64 and measured 3% slower in FP32)
+            // (d) divergence and stage combine
             if (active) {
                 const long long c = zk + own;
-                T cin[NQ], cun[NQ];
-                load_cell(a.uin, a.ncell, c, cin);
+                T cun[NQ];
+                if (!EARLY_IN) load_cell(a.uin, a.ncell, c, cin);
                 if (KIND != 1) load_cell(a.un, a.ncell, c, cun);
                 update(k, c, cin, cun, Fzp);
             }
