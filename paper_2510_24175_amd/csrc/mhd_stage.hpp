@@ -562,13 +562,16 @@ stage_kernel(const StageArgs<T> a)
     // PLM.  Per plane: the x and y faces from the LDS plane, then the z face,
     // the update and the next plane's primitives.  The own cells of plane k+2
     // are loaded before the x and y faces and used after them, so that their
-    // latency hides behind the faces; FP32 also loads the halo cells of plane
-    // k+1 and Un before the z face (FP64 lacks the registers).  Each cell is
+    // latency hides behind the faces; the halo cells of plane k+1 are loaded
+    // before the z face in FP32, with Un, and after it in FP64, before the update
+    // (128^3 step 333 -> 317 us against after the update, where they wait for its
+    // stores; before the z face 256^3 stages 1.26 + 1.39 ms against 1.23 + 1.36).
+    // Each cell is
     // read once as an own cell and once per halo that holds it: 512^3 FP32
     // fetches 7.9 GB in the first stage (4.8 compulsory) against 11.8 when the
     // combine re-read the state, and the stages take 3.83 + 4.55 ms against
     // 4.30 + 5.42 with the z face first, the re-read and 4-row tiles (256^3
-    // FP64 1.22 + 1.45 against 1.37 + 1.64).  About 70% of the time is VALU
+    // FP64 1.23 + 1.36 against 1.37 + 1.64).  About 70% of the time is VALU
     // issue (3.2 face rounds of ~270 instructions per 64 cells), the rest
     // waits for LDS, barriers and memory.
     if constexpr (!WENO) {
@@ -670,6 +673,7 @@ stage_kernel(const StageArgs<T> a)
                     else
                         face_flux<T, SOLVER>(VL, VR, 2, a.ph, Fzp);
                 }
+                if (!EARLY && k + 1 < k1) load_halo(zoff(k + 1), hu);
                 if (active) {
                     if (!EARLY && KIND != 1) load_cell(a.un, a.ncell, c, cun);
                     if (ME_LDS) {
@@ -692,10 +696,7 @@ stage_kernel(const StageArgs<T> a)
                 }
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) un1[q] = un2[q];
-                if (k + 1 < k1) {
-                    if (!EARLY) load_halo(zoff(k + 1), hu);
-                    put_halo(hu);
-                }
+                if (k + 1 < k1) put_halo(hu);
                 __syncthreads();
             }
         }
