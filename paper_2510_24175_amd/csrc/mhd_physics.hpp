@@ -42,30 +42,36 @@ template <> struct Num<float> {
 };
 
 template <> struct Num<double> {
-    // reciprocal: the hardware estimate y (relative error up to 2^-24.1) with
-    // a third-order correction, y (1 + e + e^2) with e = 1 - x y exact; the
-    // IEEE quotient on all but 529 of 2M samples in [1e-297, 1e297], within
-    // half an ulp on every one, as two Newton steps (one operation more)
+    // reciprocal: the hardware estimate (relative error up to 2^-24.3)
+    // refined by two Newton-Raphson steps (e = 1 - x r, r <- r + r e): the IEEE
+    // quotient on every one of 2^34 samples of [0.25, 0.5) (the steps commute
+    // with powers of two) and of 4M log-uniform ones in [1e-297, 1e297].  A
+    // third-order correction of the estimate, one operation shorter, is an ulp
+    // off on 186 of them.
     static __device__ __forceinline__ double rcp(double x)
     {
-        const double y = __builtin_amdgcn_rcp(x);
-        const double e = __builtin_fma(-x, y, 1.0);
-        return __builtin_fma(y, __builtin_fma(e, e, e), y);
+        double r = __builtin_amdgcn_rcp(x);
+        double e = __builtin_fma(-x, r, 1.0);
+        r = __builtin_fma(r, e, r);
+        e = __builtin_fma(-x, r, 1.0);
+        return __builtin_fma(r, e, r);
     }
     // square root: one Goldschmidt step from the hardware reciprocal-square-root
-    // estimate y ~ 1/sqrt(x) (g = x y -> sqrt(x), h = y/2, r = 1/2 - g h: g is then
-    // within 2^-47) and one residual correction g <- g + (x - g^2) h, whose
-    // error is h's 2^-24 of 2^-47.  The IEEE root on all but 513 of 2M samples
-    // in [1e-297, 1e297], within half an ulp on every one, as with h refined
-    // and a second correction (three operations more).  x + DBL_MIN keeps the
-    // estimate finite at x = 0 (result 0); negative x gives NaN; subnormal
-    // results lose bits (the kernels' roots are of sums with normal terms).
+    // estimate y ~ 1/sqrt(x) (relative error up to 2^-24.1; g = x y -> sqrt(x),
+    // h = y/2 -> 1/(2 sqrt(x)), r = 1/2 - g h, both then within 2^-46) and one
+    // residual correction g <- g + (x - g^2) h.  The IEEE root on every one of
+    // 2^34 samples of [0.25, 1) (powers of four commute) and of 4M log-uniform
+    // ones in [1e-297, 1e297]; with h left at the estimate, one operation
+    // shorter, 355 are an ulp off.  x + DBL_MIN keeps the estimate finite at x = 0
+    // (result 0); negative x gives NaN; subnormal results lose bits (the
+    // kernels' roots are of sums with normal terms).
     static __device__ __forceinline__ double sqrt(double x)
     {
         const double y = __builtin_amdgcn_rsq(x + 2.2250738585072014e-308);
-        double g = x * y;
-        const double h = 0.5 * y;
-        g = __builtin_fma(g, __builtin_fma(-g, h, 0.5), g);
+        double g = x * y, h = 0.5 * y;
+        const double r = __builtin_fma(-g, h, 0.5);
+        g = __builtin_fma(g, r, g);
+        h = __builtin_fma(h, r, h);
         return __builtin_fma(__builtin_fma(-g, g, x), h, g);
     }
     // reciprocal square root: y (1 + e/2 + 3/8 e^2), e = 1 - x y^2; within 1.0
