@@ -86,7 +86,7 @@ __device__ __forceinline__ bool cell_speeds(const T *u, double gamma, const doub
                                             double &smax, double &cmax)
 {
     const double rho = (double)u[RHO];
-    const double ir = Num<double>::rcp(rho);
+    const double ir = 1.0 / rho;
     const double m[3] = {(double)u[MX], (double)u[MY], (double)u[MZ]};
     const double b[3] = {(double)u[BX], (double)u[BY], (double)u[BZ]};
     const double bsq = b[0] * b[0] + b[1] * b[1] + b[2] * b[2];

@@ -42,3 +42,10 @@ def test_reciprocal_of_the_density(rho):
 def test_square_root(x):
     x = float.fromhex(x)
     assert sound_speed(1.0, 0.5 * x) == np.sqrt(x)
+
+
+@pytest.mark.parametrize("rho", [2.3e-308, 1.5e-308, 6e-309, 1e299])
+def test_densities_at_the_ends_of_the_range(rho):
+    """p = rho / 2: the speed is one, up to the rounding of 1 / rho (half an ulp),
+    of its product with 2 p and of the roots."""
+    assert abs(sound_speed(rho, 0.5 * rho) - 1.0) <= 4 * 2.0 ** -53
