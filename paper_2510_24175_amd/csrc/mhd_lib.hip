@@ -22,6 +22,7 @@ using namespace mhd;
 struct mhd_ctx {
     mhd_config cfg;
     hipStream_t stream = nullptr;
+    bool blocking = false;       // stream is not the null stream and waits for its work (see use_stream)
     int device = 0;
     long long n[3] = {1, 1, 1};
     long long ncell = 0;
@@ -523,10 +524,33 @@ mhd_status launch_cfl(mhd_ctx *ctx, const T *U)
     return MHD_OK;
 }
 
+// Set the stream that calls enqueue on.  Work put on a blocking stream waits
+// for the null stream's; a stream whose flags cannot be read counts as one.
+void use_stream(mhd_ctx *ctx, hipStream_t stream)
+{
+    ctx->stream = stream;
+    ctx->blocking = false;
+    if (stream) {
+        unsigned flags = 0;
+        if (hipStreamGetFlags(stream, &flags) != hipSuccess) {
+            (void)hipGetLastError();
+            flags = hipStreamDefault;
+        }
+        ctx->blocking = !(flags & hipStreamNonBlocking);
+    }
+}
+
 // Wait for the stream, after which host_res holds the results of the last
-// final reductions, and report (and clear) the flag.
+// final reductions, and report (and clear) the flag.  The step may be on
+// another stream (mhd_set_stream since, or a graph replayed elsewhere): on the
+// null stream the wait covers the blocking streams, but on a blocking stream
+// only work waits for the null stream's, so some is put there.
 mhd_status sync_results(mhd_ctx *ctx)
 {
+    if (ctx->blocking) {
+        hipLaunchKernelGGL(stream_order_kernel, dim3(1), dim3(64), 0, ctx->stream);
+        HIP_TRY(ctx, hipGetLastError());
+    }
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     int flag;
     std::memcpy(&flag, ctx->host_res + RES_FLAG, sizeof(int));
@@ -728,7 +752,7 @@ mhd_status mhd_init(const mhd_config *cfg, void *hip_stream, mhd_ctx **out)
     mhd_ctx *ctx = new (std::nothrow) mhd_ctx();
     if (!ctx) return MHD_ERR_HIP;
     ctx->cfg = *cfg;
-    ctx->stream = (hipStream_t)hip_stream;
+    use_stream(ctx, (hipStream_t)hip_stream);
     ctx->device = dev;
     ctx->ncell = 1;
     ctx->cell_volume = 1.0;
@@ -779,7 +803,7 @@ void mhd_destroy(mhd_ctx *ctx)
 mhd_status mhd_set_stream(mhd_ctx *ctx, void *hip_stream)
 {
     if (!ctx) return MHD_ERR_ARG;
-    ctx->stream = (hipStream_t)hip_stream;
+    use_stream(ctx, (hipStream_t)hip_stream);
     return MHD_OK;
 }
 

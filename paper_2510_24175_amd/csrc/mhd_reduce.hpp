@@ -45,6 +45,9 @@ cfl_kernel(const T *__restrict__ U, long long ncell, double gamma, double idx0, 
 // caller may capture it in a HIP graph).
 __global__ void clear_flag_kernel(int *flag) { *flag = 0; }
 
+// Takes its place in a stream and does nothing.
+__global__ void stream_order_kernel() {}
+
 // Folds nblocks partials of quantity blockIdx.x into out[blockIdx.x] in a
 // fixed order: each thread runs over a strided subset sequentially, then the
 // waves and their results.  Bound by the latency of its loads: a workgroup
