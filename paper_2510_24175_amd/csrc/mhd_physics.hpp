@@ -226,11 +226,13 @@ template <int LIM, typename T> __device__ __forceinline__ T limited_slope(T a, T
 // The weights are multiplied through by (beta0+eps)(beta1+eps)(beta2+eps),
 // W_k = prod_{j != k}(beta_j + eps) (beta_k + eps + tau5) (formed as the triple product
 // plus tau5 times the pair product), and the linear weights are folded into
-// the candidate deviations and the weight sums.  FP64 normalises both faces
+// the candidate deviations and the weight sums.  The indicators are formed
+// four times as large (one operation fewer); FP64 takes the resulting 64 out
+// of the linear weights.  FP64 normalises both faces
 // with one reciprocal of the product of the two weight sums: it lies between
-// (4 eps)^6 and about 4 (4 beta_max)^6, so it and its reciprocal stay normal for
-// indicators between eps and 2e50 (differences of 1e25 between neighbouring
-// cell values).  FP32 caps the indicators at 2e37 (differences beyond 1e18;
+// eps^6 and about 4 beta_max^6, so it and its reciprocal stay normal for
+// indicators between eps and 1e51 (differences of a few 1e25 between
+// neighbouring cell values).  FP32 caps the indicators at 2e37 (differences beyond 1e18;
 // squares of larger ones overflow, and the reciprocal of a sum above 8e37 is
 // subnormal), divides them by their sum and adds 1e-18:
 // the largest is then between 1/3 and 1, products of two are at least 1e-36,
@@ -269,14 +271,15 @@ __device__ __forceinline__ void wenoz_pair(T v0, T v1, T v2, T v3, T v4, T &rgt,
     const T p12 = B1 * B2, p02 = B0 * B2, p01 = B0 * B1, P = B0 * p12;
     const T w0 = tau * p12 + P, w1 = tau * p02 + P, w2 = tau * p01 + P;
     // candidate deviations from v2 at the two faces, each scaled by its
-    // linear weight ((1, 6, 3)/10 right, (3, 6, 1)/10 left)
-    const T g0 = T(0.025) * G0, g1 = T(0.15) * G1, g2 = T(0.025) * G2;
-    const T d0r = e0 * T(0.1 / 12.0) + g0, d0l = e0 * T(0.3 / 12.0) - T(3) * g0;
-    const T d1r = e1 * T(0.05) - g1, d1l = e1 * T(0.05) + g1;
-    const T d2r = e2 * T(0.3 / 12.0) - T(3) * g2, d2l = e2 * T(0.1 / 12.0) + g2;
-    const T s1 = T(0.6) * w1;
+    // linear weight ((1, 6, 3)/10 right, (3, 6, 1)/10 left), and in FP64 by 1/64
+    constexpr T k = sizeof(T) == 8 ? T(0.015625) : T(1);
+    const T g0 = T(0.025) * k * G0, g1 = T(0.15) * k * G1, g2 = T(0.025) * k * G2;
+    const T d0r = e0 * (T(0.1 / 12.0) * k) + g0, d0l = e0 * (T(0.3 / 12.0) * k) - T(3) * g0;
+    const T d1r = e1 * (T(0.05) * k) - g1, d1l = e1 * (T(0.05) * k) + g1;
+    const T d2r = e2 * (T(0.3 / 12.0) * k) - T(3) * g2, d2l = e2 * (T(0.1 / 12.0) * k) + g2;
+    const T s1 = T(0.6) * k * w1;
     const T nr = w0 * d0r + w1 * d1r + w2 * d2r, nl = w0 * d0l + w1 * d1l + w2 * d2l;
-    const T sr = T(0.1) * w0 + (T(0.3) * w2 + s1), sl = T(0.3) * w0 + (T(0.1) * w2 + s1);
+    const T sr = T(0.1) * k * w0 + (T(0.3) * k * w2 + s1), sl = T(0.3) * k * w0 + (T(0.1) * k * w2 + s1);
     if constexpr (sizeof(T) == 8) {
         const T inv = Num<T>::rcp(sr * sl);
         rgt = v2 + nr * (sl * inv);
