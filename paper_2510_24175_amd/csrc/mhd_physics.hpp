@@ -232,15 +232,15 @@ template <int LIM, typename T> __device__ __forceinline__ T limited_slope(T a, T
 // with one reciprocal of the product of the two weight sums: it lies between
 // eps^6 and about 4 beta_max^6, so it and its reciprocal stay normal for
 // indicators between eps and 1e51 (differences of a few 1e25 between
-// neighbouring cell values).  FP32 caps the indicators at 2e37 (differences beyond 1e18;
-// squares of larger ones overflow, and the reciprocal of a sum above 8e37 is
-// subnormal), divides them by their sum and adds 1e-18:
-// the largest is then between 1/3 and 1, products of two are at least 1e-36,
-// and the largest weight is at least 3e-19 times tau5.  The floor only binds
-// where an indicator is 1e18 times below the sum, that is where its candidate
-// is flat to far below FP32 resolution of the others'.  One
-// reciprocal instead of three: 63 operations and 3 reciprocals a pair instead
-// of 64 and 5 (8.2 cycles each), 256^3 stages 1.59 + 1.70 -> 1.50 + 1.60 ms.
+// neighbouring cell values).  FP32 divides the indicators by a sixteenth of
+// their sum and adds 1.6e-17: the largest is then between 5 and 16, products of
+// two stay normal, and the floor only binds where an indicator is 1e18 times
+// below the sum, that is where its candidate is flat to far below FP32
+// resolution of the others'.  The sixteenth keeps the sum's reciprocal normal
+// for indicators up to 8e37 (a quarter of FLT_MAX; differences of 5e18 to 9e18);
+// larger ones are capped there.  One reciprocal instead of three: 64
+// operations and 3 reciprocals a pair instead of 64 and 5 (8.2 cycles each),
+// 256^3 stages 1.59 + 1.70 -> 1.50 + 1.60 ms.
 template <typename T>
 __device__ __forceinline__ void wenoz_pair(T v0, T v1, T v2, T v3, T v4, T &rgt, T &lft)
 {
@@ -256,15 +256,16 @@ __device__ __forceinline__ void wenoz_pair(T v0, T v1, T v2, T v3, T v4, T &rgt,
     auto beta = [&](T e, T G) -> T { return sizeof(T) == 8 ? c * e * e + (G * G + eps) : (c * e * e + G * G) + eps; };
     T B0 = beta(e0, G0), B1 = beta(e1, G1), B2 = beta(e2, G2);
     if constexpr (sizeof(T) == 4) {
-        // relative to their sum and at least 1e-18 of it, so that the products
-        // of two stay normal
-        B0 = Num<T>::min(B0, T(2e37));
-        B1 = Num<T>::min(B1, T(2e37));
-        B2 = Num<T>::min(B2, T(2e37));
-        const T s = Num<T>::rcp(B0 + B1 + B2);
-        B0 = B0 * s + T(1e-18);
-        B1 = B1 * s + T(1e-18);
-        B2 = B2 * s + T(1e-18);
+        // relative to a sixteenth of their sum and at least 1e-18 of the sum,
+        // so that the products of two stay normal
+        const T top = T(3.4e38), part = T(0.0625), least = T(16) * T(1e-18);
+        B0 = Num<T>::min(B0, top);
+        B1 = Num<T>::min(B1, top);
+        B2 = Num<T>::min(B2, top);
+        const T s = Num<T>::rcp(part * B0 + part * B1 + part * B2);
+        B0 = B0 * s + least;
+        B1 = B1 * s + least;
+        B2 = B2 * s + least;
     }
     const T tau = Num<T>::abs(B0 - B2);
     // W_k = B0 B1 B2 + tau5 prod_{j != k} B_j

@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("riemann", ["hll", "hlld"])
-@pytest.mark.parametrize("dtype,m,amp", [("f64", 43, 0.8), ("f32", -10, 1.0),
+@pytest.mark.parametrize("dtype,m,amp", [("f32", 31, 1.0), ("f64", 43, 0.8), ("f32", -10, 1.0),
                                          ("f64", -10, 1.0)])
 def test_scaled_state(dtype, m, amp, riemann):
     import torch
