@@ -109,14 +109,16 @@ constexpr int MIN_PART_BLOCKS = 4096;
 // z chunks of a marching kernel over tiles_x x tiles_y column tiles: the
 // chunk length that minimises rounds x (planes per chunk + warm-up).  A
 // compute unit holds per_cu workgroups at a time; a round fills all units, and
-// a last round that leaves one workgroup (of two) per unit takes 0.6 of a
-// full one (measured, FP32 PLM).  warm is what starting a chunk costs, in
-// planes.  Chunks have at most 64 planes: longer ones measured no faster and
-// leave the last round's imbalance to chance.  Measured against 15 fixed
-// lengths (32^3 to 320^3, both precisions) the choice is within 6% of the
-// best; lengths halved from 64 until the grid had 2048 workgroups (256 for
-// the adjoint) were up to 30% slower below 200^3 and split 70 planes into 32,
-// 32 and 6.
+// a last round that leaves u of per_cu on each takes 0.2 + 0.8 u / per_cu of a
+// full one (one of two, FP32 PLM: 0.6 measured).  warm is what starting a
+// chunk costs, in planes.  Chunks have at most 64 planes: longer ones measured
+// no faster and leave the last round's imbalance to chance.  Measured against
+// up to 29 lengths from 1 to 64 in 222 combinations (8 grids in 3D, 16^3 to
+// 192^3 and thin ones, 13 in 2D, 64^2 to 2048^2; stages, adjoint, EMF and face
+// passes, both precisions) the choice is within 6.5% of the best, on average
+// within 1%; lengths halved from 64 until the grid had 2048 workgroups (256
+// for the adjoint) were up to 30% slower below 200^3 and split 70 planes into
+// 32, 32 and 6.
 Launch plan_march(long long nx, long long ny, long long nz, int ty, int per_cu, double warm)
 {
     Launch L;
@@ -131,7 +133,8 @@ Launch plan_march(long long nx, long long ny, long long nz, int ty, int per_cu, 
         const long long blocks = tiles * ((nz + kz - 1) / kz);
         if (blocks > most) break;
         const long long full = blocks / (COMPUTE_UNITS * per_cu), rest = blocks % (COMPUTE_UNITS * per_cu);
-        const double rounds = (double)full + (rest == 0 ? 0.0 : (rest <= COMPUTE_UNITS && per_cu > 1 ? 0.6 : 1.0));
+        const long long left = (rest + COMPUTE_UNITS - 1) / COMPUTE_UNITS;  // workgroups a unit in the last round
+        const double rounds = (double)full + (rest == 0 ? 0.0 : 0.2 + 0.8 * (double)left / per_cu);
         const double cost = rounds * ((double)kz + warm);
         if (L.kz == 0 || cost < best) {
             best = cost;
@@ -146,15 +149,21 @@ Launch plan_march(long long nx, long long ny, long long nz, int ty, int per_cu, 
 // Forward stages.  3D FP32 PLM: two 8-wave workgroups per unit, and the
 // warm-up (four loads, one z face, the halo) is worth 1.5 planes; FP64 PLM one;
 // WENO-Z one, with a warm-up (six loads, two reconstructions, one z face) of 2.
-// In two dimensions the march is over the tiles of a strip along y (4-row PLM
-// tiles: four FP32 workgroups per unit or two FP64 ones), whose start and
-// final reduction cost about a tile.
+// In two dimensions the march is over the tiles of a strip along y.  FP32: a
+// strip's start and final reduction cost a tile (WENO-Z) or half a tile (PLM);
+// PLM counts four workgroups per unit (its first stage's registers allow
+// four, its last stage's three).  FP64: one workgroup per unit (WENO-Z) or two
+// (PLM), and the start costs next to nothing, so that strips only grow where
+// that does not leave a unit with less (PLM MC + HLL + SSP-RK3, 4096 x 100 and 1000 x
+// 300: 108 and 81 us in strips of one tile, 139 and 103 in strips of seven
+// and five).
 Launch plan_stage(const mhd_ctx *ctx)
 {
     const bool f32 = ctx->cfg.dtype == MHD_F32, weno = ctx->cfg.limiter == MHD_WENOZ;
     const int ty = tile_rows_of(f32, weno, ctx->cfg.ndim);
     if (ctx->cfg.ndim < 3)
-        return plan_march(ctx->n[0], 1, (ctx->n[1] + ty - 1) / ty, 1, weno ? 1 : (f32 ? 4 : 2), 1.0);
+        return plan_march(ctx->n[0], 1, (ctx->n[1] + ty - 1) / ty, 1, weno ? 1 : (f32 ? 4 : 2),
+                          f32 ? (weno ? 1.0 : 0.5) : 0.1);
     return plan_march(ctx->n[0], ctx->n[1], ctx->n[2], ty, f32 && !weno ? 2 : 1, weno ? 2.0 : 1.5);
 }
 
