@@ -714,11 +714,11 @@ __global__ void __launch_bounds__(TX *TY) adj_stage_kernel(const AdjStageArgs<T>
         ok &= cons_to_prim(u, a.ph, v);
     };
     // flux cotangent of a face between cells ca and cb (-1: outside, zero).
-    // FP32 reads cell 0 for a cell outside and masks it: 18 branches around
+    // FP32 HLLD reads cell 0 for a cell outside and masks it: 18 branches around
     // the loads cost more than the loads (128^3: 700 us per step, 680 without
-    // them and with the z face before the barrier).  FP64, one wave per SIMD
-    // and no free register, keeps the branches (150 x 110 x 70: 1181 us, 1278
-    // with masks).
+    // them and with the z face before the barrier).  FP32 HLL (128^3: 618 us, 672
+    // with masks) and FP64, one wave per SIMD and no free register (150 x 110 x
+    // 70: 1181 us, 1278 with masks), keep the branches.
     auto face_g = [&](long long ca, long long cb, double idx, T *gb) {
         const double *v = PASS == 2 ? a.lamp : a.lam1;
         const unsigned ma = Bits<float>::opaque(ca >= 0 ? -1 : 0), mb = Bits<float>::opaque(cb >= 0 ? -1 : 0);
@@ -727,7 +727,7 @@ __global__ void __launch_bounds__(TX *TY) adj_stage_kernel(const AdjStageArgs<T>
         for (int q = 0; q < NQ; ++q) {
             const double sc = PASS == 2 && q == PSI ? a.damp : 1.0;
             double va = 0.0, vb = 0.0;
-            if (sizeof(T) == 4) {
+            if (sizeof(T) == 4 && SOLVER == SOLVER_HLLD) {
                 va = Bits<double>::keep(ma, v[q * a.ncell + pa]) * sc;
                 vb = Bits<double>::keep(mb, v[q * a.ncell + pb]) * sc;
                 // the rounded products, not a fused difference of them
