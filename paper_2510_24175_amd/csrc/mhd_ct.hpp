@@ -326,26 +326,29 @@ template <int KIND, typename T> __device__ __forceinline__ T rk_combine(T un, T 
 // reduces the CFL maxima (FP64 speeds of every cell) and the FP64 sums of the
 // 9 cell components into per-block partials.
 //
-// A workgroup owns a TX x TY tile of columns and marches along z.  A cell's
+// A workgroup owns a WX x TY tile of columns and marches along z.  A cell's
 // six faces take the EMFs of its lower edges and of those one cell up along
-// each axis: the EMFs of plane k+1 on the tile's (TX + 1) x (TY + 1) lower edges
+// each axis: the EMFs of plane k+1 on the tile's (WX + 1) x (TY + 1) lower edges
 // go to one of two LDS planes, and a plane's faces are formed from both.  The
 // fluxes of plane k that the EMFs of plane k+1 need (FxBz, FyBz) and the new z
 // face shared by two planes stay in registers.  Bound by memory: 15, 18 and
 // 24 elements per cell (first, middle, last stage) of which each is read or
 // written once, plus neighbours that hit L1 or L2.  Two element-wise passes
 // with the EMFs in memory between them moved 6 elements more and took 0.75 +
-// 1.28, 1.55 and 1.91 ms at 352^3 FP64.
-template <typename T, int KIND, bool LAST, bool MEAN, int TY>
-__global__ void __launch_bounds__(TX *TY) ct_update_kernel(const CTArgs<T> a, const Launch g)
+// 1.28, 1.55 and 1.91 ms at 352^3 FP64.  Tiles are 64 x 8, and 16 x 32 on grids of
+// up to 16 cells along x, where most lanes of the wider ones hold no cell
+// (8 x 256 x 256 FP32 PLM, mean EMF: 302 us a step, 369 with the wide ones;
+// 16 x 200 x 200 208 and 250).
+template <typename T, int KIND, bool LAST, bool MEAN, int WX, int TY>
+__global__ void __launch_bounds__(WX *TY) ct_update_kernel(const CTArgs<T> a, const Launch g)
 {
-    constexpr int NT = TX * TY, EX = TX + 1, NE = EX * (TY + 1), NIT = (NE + NT - 1) / NT;
+    constexpr int NT = WX * TY, EX = WX + 1, NE = EX * (TY + 1), NIT = (NE + NT - 1) / NT;
     __shared__ T E[2][3][NE];
-    const int t = threadIdx.x, tx = t % TX, ty = t / TX;
+    const int t = threadIdx.x, tx = t % WX, ty = t / WX;
     const int lb = logical_block(blockIdx.x, g.nblocks);
     const int tile_x = lb % g.tiles_x, rest = lb / g.tiles_x;
     const int tile_y = rest % g.tiles_y, chunk = rest / g.tiles_y;
-    const int i0 = tile_x * TX, j0 = tile_y * TY;
+    const int i0 = tile_x * WX, j0 = tile_y * TY;
     const int k0 = chunk * g.kz, k1 = min(k0 + g.kz, a.nz);
     const long long nc = a.ncell, nxy = (long long)a.nx * a.ny;
 
@@ -459,20 +462,20 @@ __global__ void __launch_bounds__(TX *TY) ct_update_kernel(const CTArgs<T> a, co
     }
     if (!ok) *a.flag = 1;
     if (LAST) {
-        __shared__ double red[TY][NPART];
+        __shared__ double red[NT / 64][NPART];
         double vals[NPART];
         vals[0] = wave_max(smax);
         vals[1] = wave_max(cmax);
 #pragma unroll
         for (int q = 0; q < NQ; ++q) vals[2 + q] = wave_sum(sum[q]);
-        if (tx == 0) {
+        if ((t & 63) == 0) {
 #pragma unroll
-            for (int x = 0; x < NPART; ++x) red[ty][x] = vals[x];
+            for (int x = 0; x < NPART; ++x) red[t / 64][x] = vals[x];
         }
         __syncthreads();
         if (t < NPART) {
             double r = red[0][t];
-            for (int w = 1; w < TY; ++w) r = t < 2 ? __builtin_fmax(r, red[w][t]) : r + red[w][t];
+            for (int w = 1; w < NT / 64; ++w) r = t < 2 ? __builtin_fmax(r, red[w][t]) : r + red[w][t];
             a.part[(long long)t * g.nblocks + lb] = r;
         }
     }

@@ -64,8 +64,10 @@ constexpr int RES_CFL = NPART, RES_FLAG = 2 * NPART, RES_WORDS = 2 * NPART + 1;
 // rows of an upwind EMF tile (TX x 8 columns: 124 KB of LDS in FP64, one
 // workgroup of 8 waves per compute unit; 62 KB in FP32, two)
 template <typename T> constexpr int ct_emf_rows() { return 8; }
-// rows of a constrained-transport update tile (64 x 8 columns)
-constexpr int CT_UPD_ROWS = 8;
+// constrained-transport update tiles: 512 columns, 64 x 8 or, on grids of up to
+// CT_THIN cells along x, CT_THIN wide (see ct_update_kernel)
+constexpr int CT_UPD_THREADS = 512, CT_THIN = 16;
+int ct_update_width(long long nx) { return nx <= CT_THIN ? CT_THIN : TX; }
 
 mhd_status fail(mhd_ctx *ctx, mhd_status st, const char *msg)
 {
@@ -119,10 +121,10 @@ constexpr int MIN_PART_BLOCKS = 4096;
 // within 1%; lengths halved from 64 until the grid had 2048 workgroups (256
 // for the adjoint) were up to 30% slower below 200^3 and split 70 planes into
 // 32, 32 and 6.
-Launch plan_march(long long nx, long long ny, long long nz, int ty, int per_cu, double warm)
+Launch plan_march(long long nx, long long ny, long long nz, int ty, int per_cu, double warm, int tx = TX)
 {
     Launch L;
-    L.tiles_x = (int)((nx + TX - 1) / TX);
+    L.tiles_x = (int)((nx + tx - 1) / tx);
     L.tiles_y = (int)((ny + ty - 1) / ty);
     const long long tiles = (long long)L.tiles_x * L.tiles_y;
     const int longest = (int)std::min(nz, 64LL);
@@ -330,17 +332,23 @@ mhd_status launch_step_ct(mhd_ctx *ctx, const T *un, T *unext, T *u1, double dt,
         HIP_TRY(ctx, hipGetLastError());
         c.uin = uin;
         c.uout = uout;
-        const dim3 grid(up.nblocks), block(TX * CT_UPD_ROWS);
         if (ctx->cfg.ct == 2) {
             hipLaunchKernelGGL((ct_emf_upwind_kernel<T, ct_emf_rows<T>()>), dim3(ug.nblocks), dim3(TX * ct_emf_rows<T>()), 0,
                                ctx->stream, c, ug);
             HIP_TRY(ctx, hipGetLastError());
-            hipLaunchKernelGGL((ct_update_kernel<T, KIND, last_stage(KIND), false, CT_UPD_ROWS>), grid, block, 0,
-                               ctx->stream, c, up);
-        } else {
-            hipLaunchKernelGGL((ct_update_kernel<T, KIND, last_stage(KIND), true, CT_UPD_ROWS>), grid, block, 0,
-                               ctx->stream, c, up);
         }
+        auto update = [&](auto mean, auto width) {
+            constexpr int WX = decltype(width)::value;
+            hipLaunchKernelGGL((ct_update_kernel<T, KIND, last_stage(KIND), decltype(mean)::value, WX, CT_UPD_THREADS / WX>),
+                               dim3(up.nblocks), dim3(CT_UPD_THREADS), 0, ctx->stream, c, up);
+        };
+        const bool thin = ct_update_width(c.nx) != TX;
+        auto with_width = [&](auto mean) {
+            if (thin) update(mean, std::integral_constant<int, CT_THIN>{});
+            else update(mean, std::integral_constant<int, TX>{});
+        };
+        if (ctx->cfg.ct == 2) with_width(std::false_type{});
+        else with_width(std::true_type{});
         HIP_TRY(ctx, hipGetLastError());
         return MHD_OK;
     };
@@ -775,7 +783,10 @@ mhd_status mhd_init(const mhd_config *cfg, void *hip_stream, mhd_ctx **out)
     // partials capacity: the forward stage grid (the CFL kernel uses at most
     // CFL_MAX_BLOCKS); the adjoint writes no partials
     ctx->plan = plan_stage(ctx);
-    if (cfg->ct) ctx->ct_plan = plan_march(ctx->n[0], ctx->n[1], ctx->n[2], CT_UPD_ROWS, 2, 1.0);
+    if (cfg->ct) {
+        const int wx = ct_update_width(ctx->n[0]);
+        ctx->ct_plan = plan_march(ctx->n[0], ctx->n[1], ctx->n[2], CT_UPD_THREADS / wx, 2, 1.0, wx);
+    }
     ctx->part_cap = std::max({ctx->plan.nblocks, ctx->ct_plan.nblocks, CFL_MAX_BLOCKS});
     ctx->ns = cfg->ct ? 12 : NQ;
     hipError_t e = hipMalloc(&ctx->u1_scratch, (size_t)ctx->ns * ctx->ncell * ctx->elem);
