@@ -190,8 +190,9 @@ mhd_status mhd_cfl_dt(mhd_ctx *ctx, const void *U, double out[2]);
  * receives the stage-1 state, which the adjoint reuses; otherwise library
  * scratch is used.  The step also reduces, on U_next, the CFL maxima and
  * the FP64 sums read back by mhd_step_info and mhd_get_sums.  With FP64
- * states every cell's speeds are formed in FP64; with FP32 states each
- * thread picks, by FP32 estimates, the cells of its column with the
+ * states, and in one and two dimensions and with constrained transport,
+ * every cell's speeds are formed in FP64; otherwise, in 3D with FP32 states,
+ * each thread picks, by FP32 estimates, the cells of its column with the
  * largest speeds and reports their FP64 speeds, so the maxima are FP64
  * speeds of actual cells, within the estimate's rounding (~1e-6 relative)
  * of the all-FP64 maxima.  MHD_ERR_ARG (nothing enqueued) for NULL or

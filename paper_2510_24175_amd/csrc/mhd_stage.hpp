@@ -490,8 +490,10 @@ stage_kernel(const StageArgs<T> a)
     }
 
     double smax = 0.0, cmax = 0.0;
-    // FP32 states: the plane (tile of the strip) of this thread's cells with the largest FP32
-    // estimates of the two maxima (their FP64 speeds are taken at the end)
+    // FP64 speeds of every cell; in 3D FP32 only of the planes of this thread's
+    // column with the largest FP32 estimates of the two maxima, taken at the end
+    // (in 1D its one cell)
+    constexpr bool ALL_SPEEDS = sizeof(T) == 8 || NDIM == 2;
     float best_s = -1.0f, best_c = -1.0f;
     int k_s = -1, k_c = -1;
     double sum[HELP_RED ? 1 : NQ];
@@ -546,7 +548,7 @@ stage_kernel(const StageArgs<T> a)
         } else if (LAST) {
 #pragma unroll
             for (int q = 0; q < NQ; ++q) sum[q] += (double)out[q];
-            if constexpr (sizeof(T) == 8) {
+            if constexpr (ALL_SPEEDS) {
                 ok &= cell_speeds<T, NDIM>(out, a.gamma_d, a.idx_d, smax, cmax);
             } else {
                 float ls, lc;
@@ -884,18 +886,17 @@ stage_kernel(const StageArgs<T> a)
         }
     }
 
-    if constexpr (LAST && sizeof(T) == 4) {
+    if constexpr (LAST && !ALL_SPEEDS) {
         // FP64 speeds of the selected cells, re-read from this thread's own
         // output (it stored them above)
-        auto cell_at = [&](int k) -> long long { return NDIM == 3 ? zoff(k) + own : own_of(k * TY); };
         if (k_s >= 0) {
             T u[NQ];
-            load_cell(a.uout, a.ncell, cell_at(k_s), u);
+            load_cell(a.uout, a.ncell, zoff(k_s) + own, u);
             ok &= cell_speeds<T, NDIM>(u, a.gamma_d, a.idx_d, smax, cmax);
         }
         if (k_c >= 0 && k_c != k_s) {
             T u[NQ];
-            load_cell(a.uout, a.ncell, cell_at(k_c), u);
+            load_cell(a.uout, a.ncell, zoff(k_c) + own, u);
             ok &= cell_speeds<T, NDIM>(u, a.gamma_d, a.idx_d, smax, cmax);
         }
     }

@@ -85,8 +85,8 @@ def check(setup, V, dtype):
     dt_all, ch_all = ctx.cfl_dt(U)
     Ug = U.double().cpu().numpy()
     ctx.close()
-    # FP32 states: the fused maxima are of the cells an FP32 estimate picks, within its rounding
-    near = 0.0 if dtype == "f64" or setup.get("ct") else 2e-6
+    # 3D FP32 states: the fused maxima are of the cells an FP32 estimate picks, within its rounding
+    near = 0.0 if dtype == "f64" or setup["ndim"] == 2 or setup.get("ct") else 2e-6
     assert abs(dt / dt_all - 1) <= near and abs(ch / ch_all - 1) <= near
     assert rel_l1(Ug[:9], Uo[:9], ho[-1][1]).max() <= TOL[dtype]
     assert max_rel(Ug[:9], Uo[:9]).max() <= TOL_MAX[dtype]
