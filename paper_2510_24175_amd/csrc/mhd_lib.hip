@@ -183,6 +183,7 @@ template <typename T> Phys<T> make_phys(const mhd_ctx *ctx, double ch)
     p.half_ich = (T)(p.glm ? 0.5 / ch : 0.0);
     p.half_ch = (T)(p.glm ? 0.5 * ch : 0.0);
     p.half_on = (T)(p.glm ? 0.5 : 0.0);
+    p.psi_bits = p.glm ? ~0u : 0u;
     return p;
 }
 

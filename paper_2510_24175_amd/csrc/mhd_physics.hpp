@@ -121,6 +121,8 @@ template <> struct Bits<float> {
     }
     // m ? a : 0
     static __device__ __forceinline__ float keep(unsigned m, float a) { return __builtin_bit_cast(float, word(a) & m); }
+    // m ? a : something finite
+    static __device__ __forceinline__ float finite_keep(unsigned m, float a) { return keep(m, a); }
     // a with its sign flipped where s is negative
     static __device__ __forceinline__ float flip(float a, float s)
     {
@@ -151,6 +153,11 @@ template <> struct Bits<double> {
         const Words x = words(a);
         return __builtin_bit_cast(double, Words{x.lo & m, x.hi & m});
     }
+    static __device__ __forceinline__ double finite_keep(unsigned m, double a)
+    {
+        const Words x = words(a);
+        return __builtin_bit_cast(double, Words{x.lo, x.hi & m});
+    }
     static __device__ __forceinline__ double flip(double a, double s)
     {
         const Words x = words(a);
@@ -169,6 +176,7 @@ template <typename T> struct Phys {
     T half_ich;  // 1 / (2 c_h), 0 when GLM is off
     T half_ch;   // c_h / 2, 0 when GLM is off
     T half_on;   // 1/2, 0 when GLM is off
+    unsigned psi_bits; // all ones, 0 when GLM is off
     int glm;     // GLM cleaning on
 };
 
@@ -539,9 +547,14 @@ __device__ __forceinline__ void face_flux(const T *VL, const T *VR, int d, const
         bns = bnf;
         psis = T(0);
     } else {
-        // GLM off: half_ich, half_on and half_ch are zero
-        bns = T(0.5) * (bnL + bnR) - (VR[PSI] - VL[PSI]) * ph.half_ich;
-        psis = ph.half_on * (VL[PSI] + VR[PSI]) - ph.half_ch * (bnR - bnL);
+        // GLM off: half_ich, half_on and half_ch are zero, and the masks keep
+        // an infinite or undefined psi (inert, it may have any size) out of
+        // their products.  A branch instead spills 12-16 registers of the FP32
+        // PLM last stage (512^3 step 8.77 -> 9.31 ms)
+        const T dp = Bits<T>::finite_keep(ph.psi_bits, VR[PSI] - VL[PSI]);
+        const T sp = Bits<T>::finite_keep(ph.psi_bits, VL[PSI] + VR[PSI]);
+        bns = T(0.5) * (bnL + bnR) - dp * ph.half_ich;
+        psis = ph.half_on * sp - ph.half_ch * (bnR - bnL);
     }
     // a face state in the frame (RState or Side)
     auto rotate = [&](const T *V, auto &s) {
