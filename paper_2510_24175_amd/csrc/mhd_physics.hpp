@@ -75,7 +75,7 @@ template <> struct Num<double> {
         return __builtin_fma(__builtin_fma(-g, g, x), h, g);
     }
     // reciprocal square root: y (1 + e/2 + 3/8 e^2), e = 1 - x y^2; within 1.0
-    // ulp for normal x > 0 (two Goldschmidt steps: 1.64, three operations
+    // ulp for normal x > 0 (two Goldschmidt steps: 1.65, three operations
     // more); NaN at 0
     static __device__ __forceinline__ double rsqrt(double x)
     {
