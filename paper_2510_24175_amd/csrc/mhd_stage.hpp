@@ -599,7 +599,9 @@ stage_kernel(const StageArgs<T> a)
         // every chunk is a single direction and the solver is inlined with a
         // compile-time frame.
         auto plane_faces = [&](int k) {
-            for (int ch = wave; ch < NCHUNK; ch += NW) {
+            // (no y faces past the row above the grid's last)
+            const int nch = NDIM == 3 ? NCHX + min(TY, a.ny - j0) + 1 : NCHUNK;
+            for (int ch = wave; ch < nch; ch += NW) {
                 if (ch < NCHX) {
                     // lanes past the last item repeat it (same values, same slot)
                     const int it = min(ch * TX + tx, NFX - 1);
