@@ -599,7 +599,8 @@ stage_kernel(const StageArgs<T> a)
         // every chunk is a single direction and the solver is inlined with a
         // compile-time frame.
         auto plane_faces = [&](int k) {
-            // (no y faces past the row above the grid's last)
+            // no y faces past those of the grid's last row (256 x 2 x 256 FP64 step
+            // 75.5 -> 60.2 us)
             const int nch = NDIM == 3 ? NCHX + min(TY, a.ny - j0) + 1 : NCHUNK;
             for (int ch = wave; ch < nch; ch += NW) {
                 if (ch < NCHX) {
